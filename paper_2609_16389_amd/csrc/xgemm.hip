@@ -485,6 +485,7 @@ struct Segment {
     int64_t grid;
     bool dma;    // pipelined direct-to-LDS kernel (else the general one)
     bool sk;     // the persistent stream-K kernel (the 256 x 256 tile; dma is set too)
+    bool vec_c;  // output 16-byte aligned, ldc a multiple of 4 (the persistent kernel's buffer stores)
     int reduce;  // 0: writes C; 1: full-matrix partials + splitk_reduce
     int dp_rounds, sk_tiles, kt;  // persistent kernel: rounds of whole tiles, shared tiles, K steps per tile
 };
@@ -628,12 +629,12 @@ int make_plan_with(int64_t M, int64_t N, int64_t K, const void *A, int64_t lda, 
             g.p.C = (float *)C;
             g.p.ldc = ldc;
             g.p.split_stride = 0;
-            g.p.vec_c = ((uintptr_t)C % 16 == 0) && (ldc % 4 == 0);
+            g.vec_c = ((uintptr_t)C % 16 == 0) && (ldc % 4 == 0);
         } else {
             g.p.C = nullptr;  // the workspace, filled in at launch
             g.p.ldc = out->ldw;
             g.p.split_stride = M * out->ldw;
-            g.p.vec_c = 1;
+            g.vec_c = true;
         }
         g.grid = count * sp;
         g.dma = dma_eligible(g.p, t.bm, pk.b);
@@ -670,7 +671,7 @@ int make_plan_with(int64_t M, int64_t N, int64_t K, const void *A, int64_t lda, 
     // with 256 of its rows within 4 GiB
     if (cfg.stream_k > 0 && cfg.tile == XGEMM_TILE_256x256 && !pk.a && !pk.b) {
         Segment &g = out->seg[0];
-        if (g.dma && M % t.bm == 0 && N % t.bn == 0 && K % t.bk == 0 && g.p.vec_c &&
+        if (g.dma && M % t.bm == 0 && N % t.bn == 0 && K % t.bk == 0 && g.vec_c &&
             (int64_t)t.bm * ldc * 4 < ((int64_t)1 << 32))
             if (sk_schedule(g, tiles, K / t.bk, cfg.stream_k == 1 ? cu_count : cfg.stream_k))
                 out->ws = sk_workspace(g);
@@ -756,17 +757,39 @@ int release_workspace(xgemm_ctx *h, hipStream_t s)
     return XGEMM_OK;
 }
 
-// Copy `batch` src_rows x src_cols operands (leading dimension ld, batch
-// stride src_stride) into dense rows x cols copies at dst (rows, cols
+// The copy of `batch` src_rows x src_cols operands (leading dimension ld,
+// batch stride src_stride) into dense rows x cols ones at dst (rows, cols
 // multiples of 8 where padded; the copies follow each other).
-hipError_t launch_pack(const void *src, int64_t ld, int64_t src_stride, int64_t src_rows, int64_t src_cols, char *dst,
-                       int64_t rows, int64_t cols, int64_t batch, hipStream_t s)
+xgemm_dev::PackOperand pack_operand(const void *src, int64_t ld, int64_t src_stride, int64_t src_rows,
+                                    int64_t src_cols, char *dst, int64_t rows, int64_t cols, int64_t batch)
 {
-    const int64_t items = batch * rows * cdiv(cols, xgemm_dev::kPackSeg);  // (problem, row, segment)
-    const int grid = (int)(items < 8192 ? items : 8192);
-    hipLaunchKernelGGL(xgemm_dev::pack16, dim3(grid), dim3(256), 0, s, (const uint16_t *)src, ld, src_stride,
-                       (int)src_rows, (int)src_cols, (uint16_t *)dst, (int64_t)cols, rows * cols, (int)rows,
-                       (int)(cols / 8), (int)batch);
+    const int64_t blocks = cdiv(batch * rows * (cols / 8), xgemm_dev::kPackBlock);
+    xgemm_dev::PackOperand o;
+    o.src = (const uint16_t *)src;
+    o.dst = (uint16_t *)dst;
+    o.lds = ld;
+    o.src_stride = src_stride;
+    o.ldd = cols;
+    o.dst_stride = rows * cols;
+    o.src_rows = (int)src_rows;
+    o.src_cols = (int)src_cols;
+    o.rows = (int)rows;
+    o.cols8 = (int)(cols / 8);
+    o.batch = (int)batch;
+    o.blocks = (int)(blocks < 16384 ? blocks : 16384);
+    return o;
+}
+
+// The copies of A and B that a plan asks for (a, b null where it does not),
+// in one launch.
+hipError_t launch_pack(const xgemm_dev::PackOperand *a, const xgemm_dev::PackOperand *b, hipStream_t s)
+{
+    xgemm_dev::PackOperand none{};
+    none.cols8 = 1;
+    const xgemm_dev::PackOperand &pa = a ? *a : none, &pb = b ? *b : none;
+    if (pa.blocks + pb.blocks == 0)
+        return hipSuccess;
+    hipLaunchKernelGGL(xgemm_dev::pack16, dim3(pa.blocks + pb.blocks), dim3(256), 0, s, pa, pb);
     return hipGetLastError();
 }
 
@@ -949,16 +972,15 @@ int launch_plan(xgemm_ctx *h, Plan plan, char *ws, int64_t M, int64_t N, int64_t
     ws = ws_data(ws);
     // operand copies for the pipelined kernels
     const Pack &pk = plan.pack;
-    if (pk.a && (e = launch_pack(A, lda, 0, M, K, ws + pk.a_off, M, pk.k8, 1, s)) != hipSuccess) {
-        set_error(h, "pack A launch", e);
-        return XGEMM_ERR_HIP;
-    }
-    if (pk.b && (e = launch_pack(B, ldb, 0, K, N, ws + pk.b_off, pk.k8, pk.n8, 1, s)) != hipSuccess) {
-        set_error(h, "pack B launch", e);
-        return XGEMM_ERR_HIP;
+    if (pk.a || pk.b) {
+        const auto pa = pack_operand(A, lda, 0, M, K, ws + pk.a_off, M, pk.k8, 1);
+        const auto pb = pack_operand(B, ldb, 0, K, N, ws + pk.b_off, pk.k8, pk.n8, 1);
+        if ((e = launch_pack(pk.a ? &pa : nullptr, pk.b ? &pb : nullptr, s)) != hipSuccess) {
+            set_error(h, "operand copy launch", e);
+            return XGEMM_ERR_HIP;
+        }
     }
 
-    const int vec_c = ((uintptr_t)C % 16 == 0) && (ldc % 4 == 0);
     for (int i = 0; i < plan.nseg; ++i) {
         Segment &g = plan.seg[i];
         if (pk.a)
@@ -978,7 +1000,7 @@ int launch_plan(xgemm_ctx *h, Plan plan, char *ws, int64_t M, int64_t N, int64_t
             const int grid = (int)(cdiv(nvec, 256) < 8192 ? cdiv(nvec, 256) : 8192);
             hipLaunchKernelGGL(xgemm_dev::splitk_reduce, dim3(grid), dim3(256), 0, s,
                                (const float *)ws, (int64_t)(M * plan.ldw), plan.ldw, g.p.split, C,
-                               ldc, (int)M, (int)N, vec_c);
+                               ldc, (int)M, (int)N);
         }
         if (g.reduce) {
             e = hipGetLastError();
@@ -1057,13 +1079,10 @@ int run_batched(xgemm_ctx *h, int64_t batch, int64_t M, int64_t N, int64_t K, co
         if (rc != XGEMM_OK)
             return rc;
         char *const w = ws_data(h->workspace);
-        e = hipSuccess;
-        if (pk.a && (e = launch_pack(A, lda, sa, M, K, w + pk.a_off, M, pk.k8, na, s)) != hipSuccess)
-            set_error(h, "pack A launch", e);
-        if (e == hipSuccess && pk.b &&
-            (e = launch_pack(B, ldb, sb, K, N, w + pk.b_off, pk.k8, pk.n8, nb, s)) != hipSuccess)
-            set_error(h, "pack B launch", e);
-        if (e != hipSuccess) {
+        const auto pa = pack_operand(A, lda, sa, M, K, w + pk.a_off, M, pk.k8, na);
+        const auto pb = pack_operand(B, ldb, sb, K, N, w + pk.b_off, pk.k8, pk.n8, nb);
+        if ((e = launch_pack(pk.a ? &pa : nullptr, pk.b ? &pb : nullptr, s)) != hipSuccess) {
+            set_error(h, "operand copy launch", e);
             (void)release_workspace(h, s);
             return XGEMM_ERR_HIP;
         }
@@ -1088,14 +1107,15 @@ int run_batched(xgemm_ctx *h, int64_t batch, int64_t M, int64_t N, int64_t K, co
     g.p.stride_a = sa;
     g.p.stride_b = sb;
     g.p.stride_c = sc;
-    // 16-byte vector paths need every problem's matrices aligned
+    // 16-byte loads need every problem's operands aligned, the persistent
+    // kernel's buffer stores every problem's C
     g.p.vec_ab = g.p.vec_ab && (sa % 8 == 0) && (sb % 8 == 0);
-    g.p.vec_c = g.p.vec_c && (sc % 4 == 0);
+    g.vec_c = g.vec_c && (sc % 4 == 0);
     g.dma = dma_eligible(g.p, kTiles[plan.tile].bm, pk.b);
     // the persistent kernel over the tiles of all problems, as xgemm_run
     // takes it for one problem with as many tiles
     const TileShape &t256 = kTiles[XGEMM_TILE_256x256];
-    if (h->persistent && !pk.a && !pk.b && g.dma && g.p.vec_c && use_persistent(M, N, K, h->cu_count, cfg, batch) &&
+    if (h->persistent && !pk.a && !pk.b && g.dma && g.vec_c && use_persistent(M, N, K, h->cu_count, cfg, batch) &&
         (int64_t)t256.bm * ldc * 4 < ((int64_t)1 << 32) &&
         sk_schedule(g, (M / t256.bm) * (N / t256.bn) * batch, K / t256.bk, h->cu_count)) {
         const size_t ws = sk_workspace(g);
