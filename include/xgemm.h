@@ -132,8 +132,8 @@ int xgemm_set_persistent(xgemm_handle_t h, int enable);
  *                A or B
  *   dtype        XGEMM_BF16 or XGEMM_FP16 (applies to A and B)
  * A pointer may be NULL only when its matrix has no elements.  Aligned fast
- * path: A, B 16-byte aligned, lda, ldb, K and N multiples of 8 (C: 16-byte
- * aligned with ldc a multiple of 4 for vector stores).  Any other layout is
+ * path: A, B 16-byte aligned, lda, ldb, K and N multiples of 8 (C: any
+ * alignment and ldc).  Any other layout is
  * still correct: the operands that miss these conditions are first copied,
  * zero-padded, into the handle's workspace (M x K rounded up to 8 for A, K x N
  * both rounded up to 8 for B; both when K is not a multiple of 8), or, where
@@ -207,8 +207,7 @@ int xgemm_run_config(xgemm_handle_t h, int64_t M, int64_t N, int64_t K,
  * paper's benchmarks include such batched products (its comparison uses a
  * strided-batched vendor GEMM with batch count L, Section 6).  All problems
  * run in one launch without split-k; the pipelined path additionally needs
- * stride_a and stride_b multiples of 8 (vector stores of C: stride_c a
- * multiple of 4).  Operands that miss the layout are copied into the
+ * stride_a and stride_b multiples of 8.  Operands that miss the layout are copied into the
  * handle's workspace as in xgemm_run, one copy per problem (one in all for
  * a stride of 0), which needs batch times the operand's padded size.
  * Errors as xgemm_run, plus XGEMM_ERR_INVALID_ARG for negative batch or
