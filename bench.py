@@ -61,7 +61,7 @@ GEMV_METRIC = "GEMV TFLOP/s and %% of the MI355X HBM-bound GEMV peak (fp32, %d²
 COUNTERS_FILE = os.path.join(ROOT, "profiles", "counters_%s.json")
 # device code whose change invalidates committed counters of each kernel
 # family (the kernel the counters describe is also named in them)
-KERNEL_SOURCES = {"gemm": ("gemm_kernel.hpp", "sk_kernel.hpp"), "gemv": ("gemv_kernel.hpp",)}
+KERNEL_SOURCES = {"gemm": ("gemm_kernel.hpp", "sk_kernel.hpp", "direct_kernel.hpp"), "gemv": ("gemv_kernel.hpp",)}
 
 
 def family(workload: str) -> str:

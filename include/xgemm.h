@@ -60,7 +60,19 @@ enum xgemm_tile {
     XGEMM_TILE_256x256 = 0,
     XGEMM_TILE_256x128 = 1,
     XGEMM_TILE_128x128 = 2,
-    XGEMM_TILE_COUNT = 3
+    XGEMM_TILE_COUNT = 3,
+    /* Blocks of C of the register-direct kernel (XGEMM_KERNEL_DIRECT).
+       xgemm_select_config does not return these; xgemm_run takes them where
+       they are faster (xgemm_launch_config), and xgemm_run_config, the tile
+       queries and the traces accept them. */
+    XGEMM_DIRECT_16x128 = 17,
+    XGEMM_DIRECT_32x64 = 18,
+    XGEMM_DIRECT_64x64 = 19,
+    XGEMM_DIRECT_64x128 = 20,
+    XGEMM_DIRECT_32x256 = 21,
+    XGEMM_DIRECT_64x256 = 22,
+    XGEMM_DIRECT_64x512 = 23,
+    XGEMM_DIRECT_END = 24
 };
 
 /*
@@ -271,6 +283,20 @@ int xgemm_select_band(int64_t M, int64_t N, int64_t K, int dtype, int cu_count, 
 int xgemm_select_plan(int64_t M, int64_t N, int64_t K, int dtype, int cu_count, int persistent, xgemm_band *out);
 
 /*
+ * The configuration of the launch xgemm_run makes for these arguments on a
+ * device with cu_count compute units (host-only; A and B are only inspected
+ * for their alignment; C taken as 16-byte aligned with ldc = N).  It is
+ * xgemm_select_band's, except where that is one launch of a tile plan and
+ * another kernel is faster for the problem and its layout: then a
+ * register-direct block (XGEMM_DIRECT_*) and the K split it runs with.  For a
+ * banded plan, the body's.  xgemm_run_config with this configuration makes
+ * the same launch.  XGEMM_ERR_INVALID_ARG for M, N or K <= 0, leading
+ * dimensions too small, cu_count < 1 or out == NULL.
+ */
+int xgemm_launch_config(int64_t M, int64_t N, int64_t K, const void *A, int64_t lda, const void *B, int64_t ldb,
+                        int cu_count, xgemm_config *out);
+
+/*
  * Workgroup tile of a tile id: rows (bm), columns (bn), K step (bk) and
  * threads per workgroup of its pipelined kernel (the general kernel, taken
  * for shapes or alignments the pipelined one does not cover, may use another
@@ -283,6 +309,9 @@ int xgemm_tile_info(int tile, int *bm, int *bn, int *bk, int *threads);
 enum xgemm_kernel_family_id {
     XGEMM_KERNEL_GENERAL = 0,    /* any shape and alignment; element-wise edge handling */
     XGEMM_KERNEL_PIPELINED = 1,  /* direct global-to-LDS loads, multi-stage LDS pipeline */
+    XGEMM_KERNEL_DIRECT = 3,     /* operands straight into registers, any layout: few output
+                                    tiles, short K; the waves of a workgroup split K and add
+                                    their sums through LDS.  N and K of at least 8. */
     XGEMM_KERNEL_PERSISTENT = 2  /* the pipelined 256 x 256 schedule as a persistent stream-K
                                     kernel.  The paper's kernels are persistent, handing out
                                     output tiles from a task generator (Section 4.2), and it

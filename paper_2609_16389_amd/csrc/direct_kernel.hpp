@@ -25,6 +25,19 @@
 // run over N reads the last NV columns and stores those of its own), and
 // the slab that runs over K is read from the last 8 values of a row and the
 // last row, shifted and zeroed.  That needs N and K of at least 8.
+//
+// What bounds it: with few rows, the bytes of B (16 x 14336 x 4096, 117 MB:
+// 25.4 us, 4.6 TB/s, against 30.1 for 128 x 128 tiles through LDS, whose A
+// tile is 7/8 padding and whose pipeline keeps 32 KiB in flight per CU; here
+// 8 waves hold 9 KiB each).  With few tiles, latency: 256^3 3.7 us against
+// 6.0, 1000^3 9.5 against 20.9 (256 workgroups against 64).  With many tiles
+// the L1 path, through which every wave pulls its own operands (64 x 128: 21
+// flop per byte), where the LDS tiles win: 2048^3 33 us against 27.  Odd
+// rows cost a slab 1.2-1.5 times its time (each 16-byte load then straddles
+// dwords); a copy of the operands costs more: 16 x 10376 x 8656 with odd
+// rows 42 us against 157.  A K split over the waves of a workgroup first,
+// because their partials meet in LDS, and over workgroups only until the
+// CUs are busy.
 #pragma once
 
 #include "gemm_kernel.hpp"
@@ -76,8 +89,9 @@ __host__ __device__ __forceinline__ u32x4 shift8_down(u32x4 v, int sh)
     return r;
 }
 
-// One workgroup (id `block` of `nblocks`), as seen by thread `tid`.
-template <int FM, int NV, int WN, int KW, int DT, class Ops>
+// One workgroup (id `block` of `nblocks`), as seen by thread `tid`.  NT: B is
+// read with streaming loads.
+template <int FM, int NV, int WN, int KW, int DT, bool NT, class Ops>
 __host__ __device__ __forceinline__ void direct_tile(const Ops &ops, const GemmParams &p_in, int block, int nblocks,
                                                      int tid)
 {
@@ -127,7 +141,8 @@ __host__ __device__ __forceinline__ void direct_tile(const Ops &ops, const GemmP
         const char *const bs = Bb + ((int64_t)k0 + 8 * S) * ldb * 2;
 #pragma unroll
         for (int r = 0; r < 8; ++r)
-            b[S][r] = ops.template gload_any<NV / 2>(bs + r * ldb * 2, b_off);
+            b[S][r] = NT ? ops.template gload_any_nt<NV / 2>(bs + r * ldb * 2, b_off)
+                         : ops.template gload_any<NV / 2>(bs + r * ldb * 2, b_off);
 #pragma unroll
         for (int i = 0; i < FM; ++i)
             a[S][i] = ops.template gload_any<4>(as, a_off[i]);
@@ -211,7 +226,7 @@ __host__ __device__ __forceinline__ void direct_tile(const Ops &ops, const GemmP
         if (row >= p.M)
             return;
         float *const c = Cb + (int64_t)row * ldc + cb + 4 * h;
-        if (cb == col && p.vec_c) {
+        if (cb == col) {
             ops.store4(c, v);
         } else {
 #pragma unroll
@@ -223,7 +238,7 @@ __host__ __device__ __forceinline__ void direct_tile(const Ops &ops, const GemmP
     // the two units of a row; where the whole block lies inside C, rearranged
     // between the lanes so that a store instruction writes 256 contiguous
     // bytes of a row, not every other 16
-    const bool whole = p.vec_c && nw + TN <= p.N;
+    const bool whole = nw + TN <= p.N;
     auto store_row = [&](int row, f32x4 v0, f32x4 v1) {
         if (whole) {
             ops.line_pair(v0, v1);
@@ -279,7 +294,7 @@ __host__ __device__ __forceinline__ void direct_tile(const Ops &ops, const GemmP
     }
 }
 
-template <int FM, int NV, int WN, int KW, int DT>
+template <int FM, int NV, int WN, int KW, int DT, bool NT>
 __global__ void __launch_bounds__(WN * KW * 64, FM *NV <= 8 ? 4 : FM *NV <= 16 ? 2 : 1)
 gemm_kernel_direct(GemmParams p_in)
 {
@@ -289,7 +304,7 @@ gemm_kernel_direct(GemmParams p_in)
     if (w >= p_in.grid)
         return;
     const DeviceOps ops{smem};
-    direct_tile<FM, NV, WN, KW, DT>(ops, p_in, w, p_in.grid, threadIdx.x);
+    direct_tile<FM, NV, WN, KW, DT, NT>(ops, p_in, w, p_in.grid, threadIdx.x);
 }
 
 }  // namespace xgemm_dev

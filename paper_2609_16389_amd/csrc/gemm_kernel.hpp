@@ -571,6 +571,38 @@ struct DeviceOps {
     // general kernel: loads into registers, LDS writes, a full barrier
     __device__ __forceinline__ u32x4 gload16(const uint16_t *q) const { return *(const u32x4 *)q; }
     __device__ __forceinline__ uint16_t gload2(const uint16_t *q) const { return *q; }
+    // D dwords at base + off, aligned to 16-bit values only.  base is uniform
+    // and kept in SGPRs with off as the lane's 32-bit offset (the empty asm
+    // hides where it comes from: folded into a 64-bit address per lane and
+    // row, the direct kernel's loads took 100 more registers and spilled)
+    template <int D>
+    __device__ __forceinline__ auto gload_any(const char *base, uint32_t off) const
+    {
+        typedef uint32_t vec __attribute__((ext_vector_type(D)));
+        struct __attribute__((packed, aligned(2))) any {
+            vec v;
+        };
+        typedef const __attribute__((address_space(1))) char *gptr;
+        gptr b = (gptr)base;
+        asm("" : "+s"(b));
+        return ((const __attribute__((address_space(1))) any *)(b + off))->v;
+    }
+    // the same, streaming (nt): for data that no other workgroup reads
+    template <int D>
+    __device__ __forceinline__ auto gload_any_nt(const char *base, uint32_t off) const
+    {
+        typedef uint32_t vec __attribute__((ext_vector_type(D)));
+        typedef vec uvec __attribute__((aligned(2)));
+        typedef const __attribute__((address_space(1))) char *gptr;
+        gptr b = (gptr)base;
+        asm("" : "+s"(b));
+        return (vec)__builtin_nontemporal_load((const __attribute__((address_space(1))) uvec *)(b + off));
+    }
+    // the low (or, if odd, the high) halves of lo and hi as one dword
+    __device__ __forceinline__ uint32_t pair16(uint32_t lo, uint32_t hi, bool odd) const
+    {
+        return __builtin_amdgcn_perm(hi, lo, odd ? 0x07060302u : 0x05040100u);
+    }
     __device__ __forceinline__ void lds_write16(char *q, u32x4 v) const { *(u32x4 *)q = v; }
     // lane-masked: only lanes with `on` write
     __device__ __forceinline__ void lds_write16(char *q, u32x4 v, bool on) const

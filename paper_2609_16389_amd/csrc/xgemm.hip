@@ -3,6 +3,7 @@
 // include/xgemm.h.
 #include <hip/hip_runtime.h>
 
+#include <math.h>
 #include <stdint.h>
 #include <stdio.h>
 #include <string.h>
@@ -14,6 +15,7 @@
 #include <vector>
 
 #include "xgemm.h"
+#include "direct_kernel.hpp"
 #include "gemm_kernel.hpp"
 #include "gemv_kernel.hpp"
 #include "pack_kernel.hpp"
@@ -75,6 +77,39 @@ constexpr TileShape kTiles[XGEMM_TILE_COUNT] = {
     {128, 128, 64, 2},  // XGEMM_TILE_128x128:  64 KiB LDS
 };
 
+// Variants of the register-direct kernel.
+template <int FM_, int NV_, int WN_, int KW_>
+struct DirectTile {
+    static constexpr int FM = FM_, NV = NV_, WN = WN_, KW = KW_, BM = 16 * FM, BN = 16 * NV * WN,
+                         THREADS = 64 * WN * KW;
+};
+
+bool is_direct(int tile) { return tile >= XGEMM_DIRECT_16x128 && tile < XGEMM_DIRECT_END; }
+
+template <class F>
+auto with_direct_tile(int tile, F &&f)
+{
+    switch (tile) {
+    case XGEMM_DIRECT_16x128: return f(DirectTile<1, 8, 1, 8>{});
+    case XGEMM_DIRECT_32x64: return f(DirectTile<2, 4, 1, 8>{});
+    case XGEMM_DIRECT_64x64: return f(DirectTile<4, 4, 1, 8>{});
+    case XGEMM_DIRECT_64x128: return f(DirectTile<4, 8, 1, 4>{});
+    case XGEMM_DIRECT_32x256: return f(DirectTile<2, 8, 2, 2>{});
+    case XGEMM_DIRECT_64x256: return f(DirectTile<4, 4, 4, 1>{});
+    default: return f(DirectTile<4, 8, 4, 1>{});   // XGEMM_DIRECT_64x512
+    }
+}
+
+TileShape tile_shape(int tile)
+{
+    if (!is_direct(tile))
+        return kTiles[tile];
+    return with_direct_tile(tile, [](auto t) {
+        using T = decltype(t);
+        return TileShape{T::BM, T::BN, 64, 1};
+    });
+}
+
 constexpr int64_t kMaxDim = (int64_t)1 << 31;
 
 int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
@@ -91,9 +126,14 @@ void set_error(xgemm_ctx *h, const char *what, hipError_t e)
 constexpr size_t kWsPrefix = 4096;
 constexpr int kMaxSkGrid = (int)(kWsPrefix / sizeof(int));
 
+bool valid_tile(int tile)
+{
+    return (tile >= 0 && tile < XGEMM_TILE_COUNT) || is_direct(tile);
+}
+
 bool valid_config(const xgemm_config *c)
 {
-    return c && c->tile >= 0 && c->tile < XGEMM_TILE_COUNT && c->split_k >= 1 && c->split_k <= 64 &&
+    return c && valid_tile(c->tile) && c->split_k >= 1 && c->split_k <= 64 &&
            c->group_m >= 1 && c->group_m <= 64 && c->stream_k >= 0 && c->stream_k < kMaxSkGrid &&
            (c->stream_k == 0 || c->split_k == 1);
 }
@@ -307,6 +347,124 @@ BandPlan select_band(int64_t M, int64_t N, int64_t K, int cu_count, bool persist
     return out;
 }
 
+// The launches xgemm_run considers beside the selected tile plan: variants of
+// the register-direct kernel.  Modelled time in microseconds: a call's start
+// (base), per round of workgroups a fixed cost and its slabs of K at a rate
+// that rises from `alone` to `full` with the share of the slots that run,
+// each slab slower by odd_a (odd_b) where rows of A (B) start on odd
+// elements, and for a K split the second launch and the partials' traffic;
+// and no less than its operands at 6.2 TB/s and C at the variant's c_tbps.
+// Fitted (least squares on log time) to 1500 to 2400 timings of each variant
+// (70 of the last) over 580 shapes: M and N 1 .. 16384, K 64 .. 65536,
+// batches up to 128, drawn evenly over their logarithms, contiguous and
+// padded, aligned and odd; rms error 8-12%.  On those shapes the launches it
+// chooses are 1.66 times faster than the tile plans (geometric mean), within
+// 6% of the fastest candidate of each, and on 2 shapes 5-6% slower than the
+// tile plan.
+struct LaunchCost {
+    int tile, slots_per_cu, chains;   // chains: partial sums per workgroup and element
+    double base, fixed, alone, full, odd_a, odd_b, split_base, split_each, us_per_byte, c_tbps;
+};
+constexpr LaunchCost kLaunchCost[] = {
+    {XGEMM_DIRECT_16x128, 2, 8, 1.60, 0.00, 1.430, 3.576, 0.292, 0.409, 2.12, 0.283, 1.11e-7, 2.24},
+    {XGEMM_DIRECT_32x64, 2, 8, 1.83, 0.00, 1.185, 3.509, 0.455, 0.186, 1.65, 0.235, 2.49e-7, 5.76},
+    {XGEMM_DIRECT_64x64, 1, 8, 1.67, 0.29, 1.930, 2.631, 0.427, 0.178, 1.37, 0.248, 3.37e-7, 1.57},
+    {XGEMM_DIRECT_64x128, 1, 4, 1.89, 1.95, 1.378, 1.959, 0.391, 0.259, 1.83, 0.197, 1.30e-7, 2.27},
+    {XGEMM_DIRECT_32x256, 2, 2, 2.46, 0.68, 0.818, 2.514, 0.387, 0.406, 1.54, 0.256, 1.11e-7, 3.08},
+    {XGEMM_DIRECT_64x256, 2, 1, 1.81, 2.80, 0.742, 2.431, 0.377, 0.236, 0.00, 0.081, 2.07e-7, 3.54},
+    {XGEMM_DIRECT_64x512, 1, 1, 0.77, 5.39, 1.157, 1.919, 0.539, 0.398, 0.00, 0.200, 2.00e-7, 5.49},
+};
+constexpr int kLaunchSplits[] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32};
+// a launch replaces the tile plan only if it is modelled this much faster
+// (at 1.0, 5 of the shapes were 5-16% slower than the tile plan)
+constexpr double kLaunchMargin = 0.92;
+
+// A time that is neither below `us` nor below the bytes' time.
+double with_floor(double us, double floor_us)
+{
+    const double a = us * us, b = floor_us * floor_us;
+    return sqrt(sqrt(a * a + b * b));
+}
+
+// Bytes of A and B, and of C.
+double operand_bytes(int64_t M, int64_t N, int64_t K, int64_t batch) { return (double)batch * 2.0 * (double)K * (double)(M + N); }
+double output_bytes(int64_t M, int64_t N, int64_t batch) { return (double)batch * 4.0 * (double)M * (double)N; }
+
+double launch_cost(const LaunchCost &c, int64_t M, int64_t N, int64_t K, int64_t batch, bool odd_a, bool odd_b,
+                   int split, int cu_count)
+{
+    const TileShape t = tile_shape(c.tile);
+    const int64_t n = cdiv(M, t.bm) * cdiv(N, t.bn) * split * batch;
+    const int64_t slots = (int64_t)cu_count * c.slots_per_cu;
+    const double slabs = (double)cdiv(cdiv(std::min(split_chunk(K, split, t.bk), K), t.bk), c.chains) *
+                         (1.0 + (odd_a ? c.odd_a : 0.0) + (odd_b ? c.odd_b : 0.0));
+    const int64_t rounds = n / slots, last = n % slots;
+    double us = c.base + (double)rounds * (c.fixed + slabs * c.full);
+    if (last > 0)
+        us += c.fixed + slabs * (c.alone + (c.full - c.alone) * (double)last / (double)slots);
+    if (split > 1)
+        us += c.split_base + c.split_each * split + (2.0 * split + 1.0) * output_bytes(M, N, 1) * c.us_per_byte;
+    return with_floor(us, 3.0 + operand_bytes(M, N, K, batch) / 6.2e6 + output_bytes(M, N, batch) / (c.c_tbps * 1e6));
+}
+
+// Modelled time of the tile plan `cfg` for these operands: the tile model,
+// no call faster than its bytes at 4.2 TB/s (few rows leave most of each
+// tile's loads to A's last row), plus the copies of operands the pipelined
+// kernels cannot read in place; for K ranges under three steps, the general
+// kernel's rounds.  Fitted to the same shapes as the launches.
+double plan_cost(int64_t M, int64_t N, int64_t K, bool copy_a, bool copy_b, int64_t batch, const xgemm_config &cfg,
+                 int cu_count)
+{
+    const TileShape &t = kTiles[cfg.tile];
+    const double floor_us = 3.0 + (operand_bytes(M, N, K, batch) + output_bytes(M, N, batch)) / 4.24e6;
+    const int64_t steps = cdiv(std::min(split_chunk(K, cfg.split_k, t.bk), K), t.bk);
+    if (steps < 3) {
+        const int64_t n = cdiv(M, t.bm) * cdiv(N, t.bn) * cfg.split_k * batch;
+        const double us = 10.0 + (double)(cdiv(n, cu_count) * steps * (t.bm * t.bn / 16384)) * 2.16 *
+                                     (copy_a || copy_b ? 1.82 : 1.0);
+        return with_floor(us, floor_us);
+    }
+    double us = with_floor(0.899 * model_cost(M * batch, N, K, cu_count, cfg.tile, cfg.split_k) + 3.03, floor_us);
+    if (copy_a || copy_b)
+        us += 5.26 + (double)batch * 4.0 * (double)K * ((copy_a ? (double)M : 0.0) + (copy_b ? (double)N : 0.0)) / 7.05e6;
+    return us;
+}
+
+// Replace *cfg, the tile plan's configuration for `batch` problems, by a
+// launch of the list above where the model puts one ahead.  A candidate adds
+// up an element from at least as many partial sums as the plan it replaces
+// (so its rounding error is no larger).
+void select_launch(int64_t M, int64_t N, int64_t K, const void *A, int64_t lda, int64_t sa, const void *B, int64_t ldb,
+                   int64_t sb, int64_t batch, int cu_count, xgemm_config *cfg)
+{
+    const int plan_chains = cfg->split_k * (cfg->tile == XGEMM_TILE_256x128 ? 2 : 1);
+    const bool k_ok = K % 8 == 0;
+    const bool copy_a = !(k_ok && (uintptr_t)A % 16 == 0 && lda % 8 == 0 && sa % 8 == 0);
+    const bool copy_b = !(k_ok && (uintptr_t)B % 16 == 0 && ldb % 8 == 0 && sb % 8 == 0 && N % 8 == 0);
+    const bool odd_a = (uintptr_t)A % 4 != 0 || lda % 2 != 0 || sa % 2 != 0;
+    const bool odd_b = (uintptr_t)B % 4 != 0 || ldb % 2 != 0 || sb % 2 != 0;
+    double best = kLaunchMargin * plan_cost(M, N, K, copy_a, copy_b, batch, *cfg, cu_count);
+    for (const LaunchCost &c : kLaunchCost) {
+        const TileShape t = tile_shape(c.tile);
+        const int64_t tiles = cdiv(M, t.bm) * cdiv(N, t.bn) * batch;
+        for (int split : kLaunchSplits) {
+            if (split > 1 && (batch > 1 || K < 256 * (int64_t)split || tiles * split > 4 * (int64_t)cu_count ||
+                              split_chunk(K, split, 64) * (split - 1) >= K))
+                break;
+            if (split * c.chains < plan_chains)
+                continue;
+            const double us = launch_cost(c, M, N, K, batch, odd_a, odd_b, split, cu_count);
+            if (us < best) {
+                best = us;
+                cfg->tile = c.tile;
+                cfg->split_k = split;
+                cfg->group_m = 4;
+                cfg->stream_k = 0;
+            }
+        }
+    }
+}
+
 size_t workspace_bytes(int64_t M, int64_t N, int split)
 {
     if (split <= 1)
@@ -434,9 +592,49 @@ auto with_general_tile(int tile, F &&f)
     }
 }
 
+// The register-direct kernel reads operands in any layout, but needs whole
+// vectors of 8 along K and N to read the edges from, and the byte offsets of
+// a row block of A and of a slab of B in 32 bits.
+bool direct_eligible(const GemmParams &p, int bm)
+{
+    return p.N >= 8 && p.K >= 8 && (int64_t)bm * p.lda * 2 < ((int64_t)1 << 32) &&
+           (64 * p.ldb + p.N) * 2 < ((int64_t)1 << 32);
+}
+
+// Streaming loads of B: where one row of blocks reads it once and it is too
+// large to be found again in the last-level cache (256 MB) by a later call.
+// 16 x 14336 x 4096 (117 MB) 25.4 against 27.9 us, 16 x 14336 x 16384 84.7
+// against 91.7; but 4 x 10736 x 3656 (78 MB), called again before other data
+// has replaced it, 17.6 against 15.7 for ordinary loads.
+constexpr double kStreamBytes = 96.0e6;
+
+template <int FM, int NV, int WN, int KW>
+hipError_t launch_direct(int dtype, GemmParams p, int grid, hipStream_t s)
+{
+    p.grid = grid;
+    const bool nt = FM == 1 && p.tiles_m == 1 && p.batch == 1 && 2.0 * (double)p.N * (double)p.K > kStreamBytes;
+    auto go = [&](auto dt, auto stream) {
+        hipLaunchKernelGGL(
+            (xgemm_dev::gemm_kernel_direct<FM, NV, WN, KW, decltype(dt)::value, decltype(stream)::value>),
+            grid_of(grid), dim3(WN * KW * 64), 0, s, p);
+    };
+    typedef std::integral_constant<int, 0> bf16;
+    typedef std::integral_constant<int, 1> fp16;
+    if constexpr (FM == 1) {
+        if (nt) {
+            dtype == XGEMM_BF16 ? go(bf16{}, std::true_type{}) : go(fp16{}, std::true_type{});
+            return hipGetLastError();
+        }
+    }
+    dtype == XGEMM_BF16 ? go(bf16{}, std::false_type{}) : go(fp16{}, std::false_type{});
+    return hipGetLastError();
+}
+
 // Threads per workgroup of a tile's pipelined (dma) or general kernel.
 int tile_threads(int tile, bool dma)
 {
+    if (is_direct(tile))
+        return with_direct_tile(tile, [](auto t) { return decltype(t)::THREADS; });
     if (dma)
         return with_dma_tile(tile, [](auto t) { return decltype(t)::WGM * decltype(t)::WGN * decltype(t)::KW * 64; });
     return with_general_tile(tile, [](auto t) { return decltype(t)::WGM * decltype(t)::WGN * 64; });
@@ -444,8 +642,13 @@ int tile_threads(int tile, bool dma)
 
 hipError_t launch_tile(int tile, bool dma, int dtype, const GemmParams &p, int grid, hipStream_t s)
 {
-    if (tile < 0 || tile >= XGEMM_TILE_COUNT)
+    if (!valid_tile(tile))
         return hipErrorInvalidValue;
+    if (is_direct(tile))
+        return with_direct_tile(tile, [&](auto t) {
+            using T = decltype(t);
+            return launch_direct<T::FM, T::NV, T::WN, T::KW>(dtype, p, grid, s);
+        });
     if (dma)
         return with_dma_tile(tile, [&](auto t) {
             using T = decltype(t);
@@ -563,7 +766,7 @@ int make_plan(int64_t M, int64_t N, int64_t K, const void *A, int64_t lda, const
               const float *C, int64_t ldc, const xgemm_config &cfg, int cu_count, Plan *out, bool allow_pack)
 {
     const int rc = make_plan_with(M, N, K, A, lda, B, ldb, C, ldc, cfg, cu_count, Pack{}, out);
-    if (rc != XGEMM_OK || !allow_pack || out->seg[0].dma)
+    if (rc != XGEMM_OK || !allow_pack || out->seg[0].dma || is_direct(out->tile))
         return rc;
     Pack pk;
     pk.k8 = cdiv(K, 8) * 8;
@@ -583,7 +786,7 @@ int make_plan(int64_t M, int64_t N, int64_t K, const void *A, int64_t lda, const
 int make_plan_with(int64_t M, int64_t N, int64_t K, const void *A, int64_t lda, const void *B, int64_t ldb,
                    const float *C, int64_t ldc, const xgemm_config &cfg, int cu_count, Pack pk, Plan *out)
 {
-    const TileShape &t = kTiles[cfg.tile];
+    const TileShape t = tile_shape(cfg.tile);
     const int64_t tiles_m = cdiv(M, t.bm), tiles_n = cdiv(N, t.bn);
     const int64_t tiles = tiles_m * tiles_n;
     if (pk.a || pk.b)
@@ -637,7 +840,7 @@ int make_plan_with(int64_t M, int64_t N, int64_t K, const void *A, int64_t lda, 
             g.vec_c = true;
         }
         g.grid = count * sp;
-        g.dma = dma_eligible(g.p, t.bm, pk.b);
+        g.dma = !is_direct(cfg.tile) && dma_eligible(g.p, t.bm, pk.b);
         g.sk = false;
         g.dp_rounds = g.sk_tiles = g.kt = 0;
     };
@@ -659,6 +862,11 @@ int make_plan_with(int64_t M, int64_t N, int64_t K, const void *A, int64_t lda, 
         }
         return (int)XGEMM_OK;
     };
+    if (is_direct(cfg.tile) && !direct_eligible(base, t.bm)) {
+        xgemm_config other = cfg;
+        other.tile = XGEMM_TILE_128x128;
+        return make_plan_with(M, N, K, A, lda, B, ldb, C, ldc, other, cu_count, pk, out);
+    }
     if (split > 1) {
         add(0, tiles, split, kc, 1);
         out->ws = workspace_bytes(M, N, split);
@@ -810,10 +1018,12 @@ struct CallPlan {
 };
 
 // Plan a call with K > 0 and M, N > 0 (arguments already checked): the
-// forced configuration, or the selected plan, banded or not.  Touches no
-// GPU.
+// forced configuration, or the selected plan, banded or not.  limit: bytes a
+// workspace may have (0: any); a tile plan that needs more is returned as it
+// is, for the caller to refuse, and another launch is taken in its place only
+// within it.  Touches no GPU.
 int plan_call(int cu_count, int64_t M, int64_t N, int64_t K, const void *A, int64_t lda, const void *B, int64_t ldb,
-              float *C, int64_t ldc, const xgemm_config *forced, CallPlan *cp, bool allow_sk = true)
+              float *C, int64_t ldc, const xgemm_config *forced, CallPlan *cp, bool allow_sk = true, size_t limit = 0)
 {
     BandPlan band;
     if (forced) {
@@ -823,6 +1033,7 @@ int plan_call(int cu_count, int64_t M, int64_t N, int64_t K, const void *A, int6
     }
     if (!allow_sk)
         band.body.stream_k = band.band.stream_k = 0;
+    int64_t limit_ws = limit > 0 ? (int64_t)limit - (int64_t)kWsPrefix : INT64_MAX;
     if (!forced && band.body.stream_k > 0) {
         // operands the persistent kernel cannot take as they are (alignment,
         // leading dimensions): the plan without it, banded or not
@@ -855,6 +1066,19 @@ int plan_call(int cu_count, int64_t M, int64_t N, int64_t K, const void *A, int6
         if (rc != XGEMM_OK)
             return rc;
         cp->ws = cp->plan[i].ws > cp->ws ? cp->plan[i].ws : cp->ws;
+    }
+    if (forced || cp->parts != 1 || band.body.stream_k > 0 || (int64_t)cp->ws > limit_ws)
+        return XGEMM_OK;
+    // one launch of a tile plan: another kernel where the model prefers it
+    xgemm_config cfg = band.body;
+    select_launch(M, N, K, A, lda, 0, B, ldb, 0, 1, cu_count, &cfg);
+    if (cfg.tile != band.body.tile || cfg.split_k != band.body.split_k) {
+        Plan other;
+        if (make_plan(M, N, K, A, lda, B, ldb, C, ldc, cfg, cu_count, &other, true) == XGEMM_OK &&
+            other.tile == cfg.tile && (is_direct(cfg.tile) || other.seg[0].dma) && (int64_t)other.ws <= limit_ws) {
+            cp->plan[0] = other;
+            cp->ws = other.ws;
+        }
     }
     return XGEMM_OK;
 }
@@ -902,7 +1126,7 @@ int run(xgemm_ctx *h, int64_t M, int64_t N, int64_t K, const void *A, int64_t ld
     if (K == 0)
         return launch_zero(h, M, N, C, ldc, s);
     CallPlan cp;
-    rc = plan_call(h->cu_count, M, N, K, A, lda, B, ldb, C, ldc, forced, &cp, forced || h->persistent);
+    rc = plan_call(h->cu_count, M, N, K, A, lda, B, ldb, C, ldc, forced, &cp, forced || h->persistent, h->ws_limit);
     if (rc != XGEMM_OK)
         return rc;
     if (cp.ws > 0 && (rc = acquire_workspace(h, cp.ws, s)) != XGEMM_OK)
@@ -1047,6 +1271,8 @@ int run_batched(xgemm_ctx *h, int64_t batch, int64_t M, int64_t N, int64_t K, co
     }
     xgemm_config cfg;
     select_config_batched(batch, M, N, K, h->cu_count, &cfg);
+    if (h->ws_limit == 0 && !(h->persistent && use_persistent(M, N, K, h->cu_count, cfg, batch)))
+        select_launch(M, N, K, A, lda, sa, B, ldb, sb, batch, h->cu_count, &cfg);
     Plan plan;
     rc = make_plan(M, N, K, A, lda, B, ldb, C, ldc, cfg, h->cu_count, &plan, false);
     if (rc != XGEMM_OK)
@@ -1065,7 +1291,7 @@ int run_batched(xgemm_ctx *h, int64_t batch, int64_t M, int64_t N, int64_t K, co
     pk.n8 = cdiv(N, 8) * 8;
     const int64_t na = sa == 0 ? 1 : batch, nb = sb == 0 ? 1 : batch;
     Plan packed;
-    if ((pk.a || pk.b) &&
+    if ((pk.a || pk.b) && !is_direct(plan.tile) &&
         make_plan_with(M, N, K, A, lda, B, ldb, C, ldc, cfg, h->cu_count, pk, &packed) == XGEMM_OK &&
         packed.seg[0].dma) {
         const size_t a_bytes = pk.a ? (size_t)na * (size_t)M * (size_t)pk.k8 * 2 : 0;
@@ -1111,7 +1337,7 @@ int run_batched(xgemm_ctx *h, int64_t batch, int64_t M, int64_t N, int64_t K, co
     // kernel's buffer stores every problem's C
     g.p.vec_ab = g.p.vec_ab && (sa % 8 == 0) && (sb % 8 == 0);
     g.vec_c = g.vec_c && (sc % 4 == 0);
-    g.dma = dma_eligible(g.p, kTiles[plan.tile].bm, pk.b);
+    g.dma = !is_direct(plan.tile) && dma_eligible(g.p, tile_shape(plan.tile).bm, pk.b);
     // the persistent kernel over the tiles of all problems, as xgemm_run
     // takes it for one problem with as many tiles
     const TileShape &t256 = kTiles[XGEMM_TILE_256x256];
@@ -1384,6 +1610,19 @@ struct TraceOps {
         push(XGEMM_TRACE_LOAD, 2, 0, (int64_t)(uintptr_t)q);
         return 0;
     }
+    template <int D>
+    auto gload_any(const char *base, uint32_t off) const
+    {
+        typedef uint32_t vec __attribute__((ext_vector_type(D)));
+        push(XGEMM_TRACE_LOAD, 4 * D, 0, (int64_t)((uintptr_t)base + off));
+        return vec{};
+    }
+    template <int D>
+    auto gload_any_nt(const char *base, uint32_t off) const
+    {
+        return gload_any<D>(base, off);
+    }
+    uint32_t pair16(uint32_t, uint32_t, bool) const { return 0; }
     void lds_write16(char *q, xgemm_dev::u32x4) const { push(XGEMM_TRACE_LDS_WRITE, 16, q - base, 0); }
     void lds_write16(char *q, xgemm_dev::u32x4, bool on) const
     {
@@ -1620,9 +1859,9 @@ int xgemm_run_noalloc(xgemm_handle_t h, int64_t M, int64_t N, int64_t K, const v
     if (K == 0)
         return launch_zero(h, M, N, C, ldc, s);
     CallPlan cp;
-    rc = plan_call(h->cu_count, M, N, K, A, lda, B, ldb, C, ldc, nullptr, &cp, h->persistent);
+    rc = plan_call(h->cu_count, M, N, K, A, lda, B, ldb, C, ldc, nullptr, &cp, h->persistent, kScratchBytes);
     if (rc == XGEMM_OK && cp.ws + kWsPrefix > kScratchBytes)   // a persistent plan's partials may not fit
-        rc = plan_call(h->cu_count, M, N, K, A, lda, B, ldb, C, ldc, nullptr, &cp, false);
+        rc = plan_call(h->cu_count, M, N, K, A, lda, B, ldb, C, ldc, nullptr, &cp, false, kScratchBytes);
     if (rc != XGEMM_OK)
         return rc;
     if (cp.ws + kWsPrefix > kScratchBytes) {
@@ -1682,13 +1921,32 @@ int xgemm_select_band(int64_t M, int64_t N, int64_t K, int dtype, int cu_count, 
     return xgemm_select_plan(M, N, K, dtype, cu_count, 1, out);
 }
 
+int xgemm_launch_config(int64_t M, int64_t N, int64_t K, const void *A, int64_t lda, const void *B, int64_t ldb,
+                        int cu_count, xgemm_config *out)
+{
+    if (!out || M <= 0 || N <= 0 || K <= 0 || M >= kMaxDim || N >= kMaxDim || K >= kMaxDim || cu_count < 1 ||
+        lda < K || ldb < N)
+        return XGEMM_ERR_INVALID_ARG;
+    CallPlan cp;
+    const int rc = plan_call(cu_count, M, N, K, A, lda, B, ldb, nullptr, N, nullptr, &cp);
+    if (rc != XGEMM_OK)
+        return rc;
+    const Segment &g = cp.plan[0].seg[0];
+    out->tile = cp.plan[0].tile;
+    out->split_k = g.p.split;
+    out->group_m = g.p.group_m;
+    out->stream_k = g.sk ? 1 : 0;
+    return XGEMM_OK;
+}
+
 int xgemm_tile_info(int tile, int *bm, int *bn, int *bk, int *threads)
 {
-    if (tile < 0 || tile >= XGEMM_TILE_COUNT || !bm || !bn || !bk || !threads)
+    if (!valid_tile(tile) || !bm || !bn || !bk || !threads)
         return XGEMM_ERR_INVALID_ARG;
-    *bm = kTiles[tile].bm;
-    *bn = kTiles[tile].bn;
-    *bk = kTiles[tile].bk;
+    const TileShape t = tile_shape(tile);
+    *bm = t.bm;
+    *bn = t.bn;
+    *bk = t.bk;
     *threads = tile_threads(tile, true);
     return XGEMM_OK;
 }
@@ -1703,7 +1961,7 @@ int xgemm_kernel_family(int64_t M, int64_t N, int64_t K, const void *A, int64_t 
     // C taken as aligned; the persistent kernel's grid is 256 CUs here
     if (make_plan(M, N, K, A, lda, B, ldb, nullptr, N, *cfg, 256, &plan, true) != XGEMM_OK)
         return -1;
-    return plan.seg[0].sk ? XGEMM_KERNEL_PERSISTENT : plan.seg[0].dma ? XGEMM_KERNEL_PIPELINED : XGEMM_KERNEL_GENERAL;
+    return is_direct(plan.tile) ? XGEMM_KERNEL_DIRECT : plan.seg[0].sk ? XGEMM_KERNEL_PERSISTENT : plan.seg[0].dma ? XGEMM_KERNEL_PIPELINED : XGEMM_KERNEL_GENERAL;
 }
 
 size_t xgemm_workspace_bytes(int64_t M, int64_t N, int64_t K, int cu_count, const xgemm_config *cfg)
@@ -1731,10 +1989,13 @@ int xgemm_trace_plan(int64_t M, int64_t N, int64_t K, const void *A, int64_t lda
         return rc;
     const Segment &g = plan.seg[segment];
     info->segments = plan.nseg;
-    info->family = g.sk ? XGEMM_KERNEL_PERSISTENT : g.dma ? XGEMM_KERNEL_PIPELINED : XGEMM_KERNEL_GENERAL;
+    info->family = is_direct(plan.tile) ? XGEMM_KERNEL_DIRECT : g.sk ? XGEMM_KERNEL_PERSISTENT : g.dma ? XGEMM_KERNEL_PIPELINED : XGEMM_KERNEL_GENERAL;
     info->reduce = g.reduce;
     info->threads = tile_threads(plan.tile, g.dma);
-    info->lds_bytes = g.sk ? xgemm_dev::sk_lds_bytes<kSkBM, kSkBN, kDmaBK>()
+    info->lds_bytes = is_direct(plan.tile) ? with_direct_tile(plan.tile, [](auto t) {
+        using T = decltype(t);
+        return xgemm_dev::direct_lds_bytes<T::FM, T::NV, T::WN, T::KW>();
+    }) : g.sk ? xgemm_dev::sk_lds_bytes<kSkBM, kSkBN, kDmaBK>()
                     : g.dma ? with_dma_tile(plan.tile, [](auto t) {
         using T = decltype(t);
         return xgemm_dev::dma_lds_bytes<T::BM, T::BN, T::BK, T::STAGES>();
@@ -1805,6 +2066,15 @@ int xgemm_trace_workgroup(int64_t M, int64_t N, int64_t K, const void *A, int64_
         }
         return (int)XGEMM_OK;
     };
+    if (is_direct(plan.tile))
+        return with_direct_tile(plan.tile, [&](auto t) {
+            using T = decltype(t);
+            return trace_threads(xgemm_dev::direct_lds_bytes<T::FM, T::NV, T::WN, T::KW>(),
+                                 [&](const TraceOps &ops, int tid) {
+                                     xgemm_dev::direct_tile<T::FM, T::NV, T::WN, T::KW, 0, false>(ops, g.p, (int)block,
+                                                                                          (int)g.grid, tid);
+                                 });
+        });
     if (g.sk) {
         const xgemm_dev::SkParams q = sk_params(g, (int *)W, (float *)wdata);
         const int lw = xgemm_dev::sk_logical((int)block, q.grid);

@@ -706,11 +706,12 @@ def check_gemv_launch(M, K, cfg, lda=None):
 def check_call(M, N, K, dtype=0, cu_count=256, max_blocks=None):
     """Check the launches xgemm_run makes for a call with 16-byte aligned A,
     B and C at lda = K, ldb = ldc = N: one plan, or a body and a band of C
-    (xgemm_select_band), each checked as its own call on the sub-matrix.
+    (xgemm_select_band; a single plan's launch from xgemm_launch_config), each checked as its own call on the sub-matrix.
     Returns one LaunchReport per part."""
     band = xg.xgemm_select_band(M, N, K, dtype, cu_count)
     if band.axis == xg.XGEMM_BAND_NONE:
-        return [check_launch(M, N, K, band.body, cu_count, max_blocks=max_blocks)]
+        cfg = xg.xgemm_launch_config(M, N, K, BASE_A, K, BASE_B, N, cu_count)
+        return [check_launch(M, N, K, cfg, cu_count, max_blocks=max_blocks)]
     e = band.extent
     if band.axis == xg.XGEMM_BAND_COLUMNS:
         parts = [((M, e), band.body), ((M, N - e), band.band)]

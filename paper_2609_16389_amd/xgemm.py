@@ -29,10 +29,19 @@ XGEMM_TILE_256x256 = 0
 XGEMM_TILE_256x128 = 1
 XGEMM_TILE_128x128 = 2
 XGEMM_TILE_COUNT = 3
+XGEMM_DIRECT_16x128 = 17
+XGEMM_DIRECT_32x64 = 18
+XGEMM_DIRECT_64x64 = 19
+XGEMM_DIRECT_64x128 = 20
+XGEMM_DIRECT_32x256 = 21
+XGEMM_DIRECT_64x256 = 22
+XGEMM_DIRECT_64x512 = 23
+XGEMM_DIRECT_END = 24
 
 XGEMM_KERNEL_GENERAL = 0
 XGEMM_KERNEL_PIPELINED = 1
 XGEMM_KERNEL_PERSISTENT = 2
+XGEMM_KERNEL_DIRECT = 3
 
 
 class xgemm_config(ctypes.Structure):
@@ -140,6 +149,8 @@ lib.xgemm_select_band.argtypes = [_i64, _i64, _i64, _i32, _i32, ctypes.POINTER(x
 lib.xgemm_select_plan.argtypes = [_i64, _i64, _i64, _i32, _i32, _i32, ctypes.POINTER(xgemm_band)]
 lib.xgemm_select_plan.restype = _i32
 lib.xgemm_select_band.restype = _i32
+lib.xgemm_launch_config.argtypes = [_i64, _i64, _i64, _p, _i64, _p, _i64, _i32, ctypes.POINTER(xgemm_config)]
+lib.xgemm_launch_config.restype = _i32
 lib.xgemm_tile_info.argtypes = [_i32] + [ctypes.POINTER(ctypes.c_int)] * 4
 lib.xgemm_tile_info.restype = _i32
 lib.xgemm_kernel_family.argtypes = [_i64, _i64, _i64, _p, _i64, _p, _i64, ctypes.POINTER(xgemm_config)]
@@ -240,6 +251,14 @@ def xgemm_select_band(M, N, K, dtype, cu_count) -> xgemm_band:
 def xgemm_select_plan(M, N, K, dtype, cu_count, persistent) -> xgemm_band:
     out = xgemm_band()
     rc = lib.xgemm_select_plan(M, N, K, dtype, cu_count, persistent, ctypes.byref(out))
+    if rc != XGEMM_OK:
+        raise XgemmError(rc)
+    return out
+
+
+def xgemm_launch_config(M, N, K, A, lda, B, ldb, cu_count) -> xgemm_config:
+    out = xgemm_config()
+    rc = lib.xgemm_launch_config(M, N, K, A, lda, B, ldb, cu_count, ctypes.byref(out))
     if rc != XGEMM_OK:
         raise XgemmError(rc)
     return out

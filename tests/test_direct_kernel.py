@@ -1,0 +1,122 @@
+"""The register-direct kernel: the synchronisation checker's traces (bounds of
+every load, every element of C stored once, the LDS exchange) and parity with
+the oracle, at the edges of its blocks, slabs and dispatch."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2609_16389_amd import syncheck as sc
+from paper_2609_16389_amd import workloads as wl
+from paper_2609_16389_amd import xgemm as xg
+
+DIRECT = list(range(xg.XGEMM_DIRECT_16x128, xg.XGEMM_DIRECT_END))
+
+# (M, N, K, pad of lda, of ldb, of ldc, split): the smallest sizes, one block
+# and one beyond it, a wave with no slab, partial slabs and partial vectors in
+# N, odd rows, K splits whose last range is partial
+EDGES = [(1, 8, 8, 0, 0, 0, 1), (1, 9, 9, 0, 0, 0, 1), (17, 65, 63, 3, 1, 1, 1), (64, 256, 64, 0, 0, 0, 1),
+         (65, 257, 65, 8, 8, 4, 1), (33, 129, 520, 1, 0, 0, 1), (16, 300, 1101, 0, 0, 3, 2), (70, 136, 777, 0, 3, 0, 3)]
+
+
+def _cfg(tile, split=1):
+    return xg.xgemm_config(tile, split, 4, 0)
+
+
+@pytest.mark.parametrize("tile", DIRECT)
+@pytest.mark.parametrize("case", EDGES, ids=lambda c: "x".join(map(str, c)))
+def test_traces(tile, case):
+    M, N, K, pa, pb, pc, split = case
+    info = xg.xgemm_trace_plan(M, N, K, sc.BASE_A, K + pa, sc.BASE_B, N + pb, sc.BASE_C, N + pc, _cfg(tile, split),
+                               256, 0)
+    assert info.family == xg.XGEMM_KERNEL_DIRECT and info.packed == 0
+    rep = sc.check_launch(M, N, K, _cfg(tile, split), lda=K + pa, ldb=N + pb, ldc=N + pc)
+    assert rep.ok, [str(v) for v in rep.violations]
+
+
+def test_too_small_or_too_wide_falls_back():
+    """Fewer than 8 columns or K, or rows so far apart that 32-bit offsets
+    overflow: another family runs."""
+    for M, N, K, lda, ldb in [(64, 7, 512, 512, 7), (64, 512, 7, 7, 512), (64, 64, 64, 1 << 26, 64),
+                              (64, 64, 64, 64, 1 << 26)]:
+        assert xg.xgemm_kernel_family(M, N, K, 1 << 20, lda, 1 << 20, ldb, _cfg(xg.XGEMM_DIRECT_64x64)) \
+            != xg.XGEMM_KERNEL_DIRECT
+
+
+def test_dispatch():
+    """Few output tiles take the direct kernel in any layout; whole rounds of
+    large tiles, banded and persistent plans keep theirs; a launch that
+    replaces a K-split plan adds at least as many partial sums."""
+    def launch(M, N, K, lda=None, ldb=None):
+        return xg.xgemm_launch_config(M, N, K, 1 << 20, lda or K, 1 << 20, ldb or N, 256)
+    for shape in [(256, 256, 256), (1000, 1000, 1000), (16, 4096, 4096), (1, 2496, 5751), (300, 203, 777)]:
+        assert launch(*shape).tile in DIRECT, shape
+    for shape in [(4096, 4096, 4096), (8192, 8192, 8192), (6144, 6144, 6144), (1024, 1024, 65536)]:
+        c, b = launch(*shape), xg.xgemm_select_band(*shape, xg.XGEMM_BF16, 256)
+        assert (c.tile, c.split_k, c.stream_k) == (b.body.tile, b.body.split_k, b.body.stream_k), shape
+    waves = dict(zip(DIRECT, (8, 8, 8, 4, 2, 1, 1)))
+    rng = np.random.default_rng(5)
+    for _ in range(200):
+        M, N, K = (int(2 ** rng.uniform(0, 12)) for _ in range(3))
+        c, s = launch(M, N, K), xg.xgemm_select_config(M, N, K, xg.XGEMM_BF16, 256)
+        if c.tile in DIRECT:
+            assert c.split_k * waves[c.tile] >= s.split_k
+
+
+def _operand(bits, dtype, pad):
+    import torch
+    from gpu_util import to_device
+    rows, cols = bits.shape
+    wide = np.full((rows, cols + pad), 0x7E00 if dtype == "fp16" else 0x7FC0, dtype=np.uint16)   # NaN padding
+    wide[:, :cols] = bits
+    return to_device(wide, dtype)[:, :cols]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", ["bf16", "fp16"])
+@pytest.mark.parametrize("tile", DIRECT)
+@pytest.mark.parametrize("case", EDGES, ids=lambda c: "x".join(map(str, c)))
+def test_parity(tile, case, dtype):
+    import torch
+    from gpu_util import check_close
+    M, N, K, pa, pb, pc, split = case
+    oracle.build(force=False)
+    A, B = wl.make_inputs(M, N, K, dtype, "uniform", M + N + K)
+    C_ref, S = oracle.gemm(A, B, dtype)
+    out = torch.full((M, N + pc), 7.0, dtype=torch.float32, device="cuda")
+    xg.gemm(_operand(A, dtype, pa), _operand(B, dtype, pb), out=out[:, :N], config=_cfg(tile, split))
+    torch.cuda.synchronize()
+    got = out.cpu().numpy()
+    check_close(got[:, :N], C_ref, S, "direct %d %s" % (tile, case))
+    assert np.all(got[:, N:] == 7.0)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape", [(5, 70, 264, 64), (3, 33, 137, 129), (40, 200, 72, 200)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_batched_parity(shape):
+    """Batches that take the direct kernel: every problem's block edges."""
+    import torch
+    from gpu_util import check_close, to_device
+    L, M, N, K = shape
+    oracle.build(force=False)
+    cases = [wl.make_inputs(M, N, K, "bf16", "normal", seed=b) for b in range(L)]
+    A = torch.stack([to_device(a, "bf16") for a, _ in cases])
+    B = torch.stack([to_device(b, "bf16") for _, b in cases])
+    C = xg.bmm(A, B).cpu().numpy()
+    for b, (a_bits, b_bits) in enumerate(cases):
+        C_ref, S = oracle.gemm(a_bits, b_bits, "bf16")
+        check_close(C[b], C_ref, S, "batched direct %s problem %d" % (shape, b))
+
+
+@pytest.mark.gpu
+def test_infinities_stay_in_their_rows():
+    """Zeroed lanes past K and clamped rows must not meet infinities of other
+    rows: one infinite element of A reaches its own row only."""
+    import torch
+    M, N, K = 20, 40, 75
+    A = torch.ones((M, K), dtype=torch.bfloat16, device="cuda")
+    B = torch.ones((K, N), dtype=torch.bfloat16, device="cuda")
+    A[M - 1, K - 1] = float("inf")
+    for tile in DIRECT:
+        C = xg.gemm(A, B, config=_cfg(tile))
+        assert torch.all(torch.isinf(C[M - 1])) and torch.all(C[:M - 1] == K), tile
