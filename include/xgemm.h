@@ -61,10 +61,13 @@ enum xgemm_tile {
     XGEMM_TILE_256x128 = 1,
     XGEMM_TILE_128x128 = 2,
     XGEMM_TILE_COUNT = 3,
-    /* Blocks of C of the register-direct kernel (XGEMM_KERNEL_DIRECT).
-       xgemm_select_config does not return these; xgemm_run takes them where
-       they are faster (xgemm_launch_config), and xgemm_run_config, the tile
-       queries and the traces accept them. */
+    /* Launches that xgemm_select_config does not return: xgemm_run takes them
+       where they are faster (xgemm_launch_config), and xgemm_run_config, the
+       tile queries and the traces accept them.
+       A pipelined 128 x 128 tile for at most one workgroup per CU: eight
+       waves, pairs of which split every K step, and four LDS stages. */
+    XGEMM_TILE_128x128_K2 = 16,
+    /* Blocks of C of the register-direct kernel (XGEMM_KERNEL_DIRECT). */
     XGEMM_DIRECT_16x128 = 17,
     XGEMM_DIRECT_32x64 = 18,
     XGEMM_DIRECT_64x64 = 19,
@@ -287,8 +290,9 @@ int xgemm_select_plan(int64_t M, int64_t N, int64_t K, int dtype, int cu_count, 
  * device with cu_count compute units (host-only; A and B are only inspected
  * for their alignment; C taken as 16-byte aligned with ldc = N).  It is
  * xgemm_select_band's, except where that is one launch of a tile plan and
- * another kernel is faster for the problem and its layout: then a
- * register-direct block (XGEMM_DIRECT_*) and the K split it runs with.  For a
+ * another kernel is faster for the problem and its layout: then
+ * XGEMM_TILE_128x128_K2 or a register-direct block (XGEMM_DIRECT_*) and the K
+ * split it runs with.  For a
  * banded plan, the body's.  xgemm_run_config with this configuration makes
  * the same launch.  XGEMM_ERR_INVALID_ARG for M, N or K <= 0, leading
  * dimensions too small, cu_count < 1 or out == NULL.

@@ -1113,25 +1113,26 @@ __host__ __device__ __forceinline__ void dma_tile(const Ops &ops, const GemmPara
         // Two waves per SIMD on a tile too narrow for two 128 x 64 blocks
         // per SIMD: the waves of a pair own the same 128 x 64 block and
         // split every K step, wave wk multiplying sub-step wk (32 of the 64
-        // k).  Each wave thus reads the LDS bytes per flop of a 128 x 64
+        // k).  Each wave thus reads the LDS bytes per flop of a whole
         // block, and the other wave of its SIMD covers its barrier and load
-        // waits.  Three stages: the loads of step t+3 go into the stage that
-        // step t's barrier frees (its fragments were read during step t-1)
-        // and have two steps to land.  A wave's fragments of step t+1 are
+        // waits.  Three or four stages: the loads of step t+STAGES go into the
+        // stage that step t's barrier frees (its fragments were read during
+        // step t-1) and have STAGES - 1 steps to land.  A wave's fragments of step t+1 are
         // read during step t into the other register buffer, so the buffer
         // alternates with the step's parity (a template argument: register
         // arrays are not indexed at run time).
         constexpr int R = 1;                      // rows of a step issued before its barrier
-        static_assert(MI == 16 && STAGES == 3 && KS == 2 && FN <= FM - R && FM % 2 == 0, "K-pair schedule shape");
+        static_assert(MI == 16 && STAGES >= 3 && STAGES <= 4 && KS == 2 && FM % 2 == 0, "K-pair schedule shape");
+        constexpr int BR = (FN + FM - R - 1) / (FM - R);   // B blocks read per row after the barrier
         constexpr int LSTEP = ((FM - R) * FN) / LD > 0 ? ((FM - R) * FN) / LD : 1;
         static_assert(LSTEP * (LD - 1) < (FM - R) * FN, "load spacing");
         u32x4 ga[2][FM], gb[2][FN];
         // One K step t in buffer BUF (t's parity).  LOAD: issue the loads of
-        // step t+3 into stage t % 3.  WAIT: this wave's load groups allowed
+        // step t+STAGES into stage t % STAGES.  WAIT: this wave's load groups allowed
         // in flight once step t+1 has landed (-1: t is the last step).
         auto kstep_k = [&]<int BUF, bool LOAD, int WAIT>(int t) {
-            const int stage = t % 3;
-            const int next = stage == 2 ? 0 : stage + 1;
+            const int stage = t % STAGES;
+            const int next = stage == STAGES - 1 ? 0 : stage + 1;
 #pragma unroll
             for (int i = 0; i < R; ++i) {
 #pragma unroll
@@ -1159,23 +1160,31 @@ __host__ __device__ __forceinline__ void dma_tile(const Ops &ops, const GemmPara
                     const int g = (i - R) * FN + j;
                     if constexpr (LOAD) {
                         if (g % LSTEP == 0 && g / LSTEP < LD)
-                            load_j(t + 3, stage, g / LSTEP);
+                            load_j(t + STAGES, stage, g / LSTEP);
                     }
                 }
                 if constexpr (WAIT >= 0) {
                     ga[BUF ^ 1][i] = frag_A(next, wk, i);
-                    if (i - R < FN)
-                        gb[BUF ^ 1][i - R] = frag_B(next, wk, i - R);
+#pragma unroll
+                    for (int j = (i - R) * BR; j < (i - R + 1) * BR && j < FN; ++j)
+                        gb[BUF ^ 1][j] = frag_B(next, wk, j);
                 }
                 ops.fence();
             }
             ops.template priority<0>();
         };
-        // the last three steps: no more loads, then exact waits
-        auto last3 = [&]<int BUF>(int t) {
-            kstep_k.template operator()<BUF, false, 1>(t);
-            kstep_k.template operator()<BUF ^ 1, false, 0>(t + 1);
-            kstep_k.template operator()<BUF, false, -1>(t + 2);
+        // the last STAGES steps: no more loads, then exact waits
+        auto last_steps = [&]<int BUF>(int t) {
+            if constexpr (STAGES == 4) {
+                kstep_k.template operator()<BUF, false, 2>(t);
+                kstep_k.template operator()<BUF ^ 1, false, 1>(t + 1);
+                kstep_k.template operator()<BUF, false, 0>(t + 2);
+                kstep_k.template operator()<BUF ^ 1, false, -1>(t + 3);
+            } else {
+                kstep_k.template operator()<BUF, false, 1>(t);
+                kstep_k.template operator()<BUF ^ 1, false, 0>(t + 1);
+                kstep_k.template operator()<BUF, false, -1>(t + 2);
+            }
         };
         // Add the pair's sums through LDS (every stage is free once every
         // wave is past the last step's barrier, which follows its last
@@ -1206,12 +1215,12 @@ __host__ __device__ __forceinline__ void dma_tile(const Ops &ops, const GemmPara
                     acc[h][j] = WK ? other + acc[KEEP + h][j] : acc[KEEP + h][j] + other;
                 }
         };
-        // Steps 0 .. nk-4 issue loads (nl of them).  The K loop is
+        // Steps 0 .. nk-STAGES-1 issue loads (nl of them).  The K loop is
         // instantiated per parity of nl: the fragment buffers alternate with
         // the step, and with an odd nl step 0 runs from buffer 1, so that the
-        // loop of two steps and the last three always start from buffer 0.
-        // The loop body runs at least once (nk = 3 and 4 are straight-line
-        // code of their own): a path that skipped it kept the first
+        // loop of two steps and the last STAGES always start from buffer 0.
+        // The loop body runs at least once (nk = STAGES and STAGES + 1 are
+        // straight-line code of their own): a path that skipped it kept the first
         // fragments live across it and spilled.  After the last step only the
         // accumulators are live, and the exchange is instantiated per wk.
         // (buffer 1 is read B first: the branches then begin differently, so
@@ -1233,35 +1242,35 @@ __host__ __device__ __forceinline__ void dma_tile(const Ops &ops, const GemmPara
             }
         };
         auto k_loop = [&]<int P>() {
-            const int nl = nk - 3;
+            const int nl = nk - STAGES;
             first_frags.template operator()<P>();
             int t = 0;
             if constexpr (P == 1) {
-                kstep_k.template operator()<1, true, 1>(0);
+                kstep_k.template operator()<1, true, STAGES - 2>(0);
                 t = 1;
             }
             do {
-                kstep_k.template operator()<0, true, 1>(t);
-                kstep_k.template operator()<1, true, 1>(t + 1);
+                kstep_k.template operator()<0, true, STAGES - 2>(t);
+                kstep_k.template operator()<1, true, STAGES - 2>(t + 1);
                 t += 2;
             } while (t + 2 <= nl);
-            last3.template operator()<0>(t);
+            last_steps.template operator()<0>(t);
         };
-        if (nk >= 3) {
-            issue_loads(0, 0);
-            issue_loads(1, 1);
-            issue_loads(2, 2);
-            ops.template wait_vm<2 * LD>();
+        if (nk >= STAGES) {
+#pragma unroll
+            for (int t = 0; t < STAGES; ++t)
+                issue_loads(t, t);
+            ops.template wait_vm<(STAGES - 1) * LD>();
             ops.barrier();
             zero_partial();
-            if (nk == 3) {
+            if (nk == STAGES) {
                 first_frags.template operator()<0>();
-                last3.template operator()<0>(0);
-            } else if (nk == 4) {
+                last_steps.template operator()<0>(0);
+            } else if (nk == STAGES + 1) {
                 first_frags.template operator()<1>();
-                kstep_k.template operator()<1, true, 1>(0);
-                last3.template operator()<0>(1);
-            } else if ((nk - 3) & 1) {
+                kstep_k.template operator()<1, true, STAGES - 2>(0);
+                last_steps.template operator()<0>(1);
+            } else if ((nk - STAGES) & 1) {
                 k_loop.template operator()<1>();
             } else {
                 k_loop.template operator()<0>();

@@ -102,6 +102,8 @@ auto with_direct_tile(int tile, F &&f)
 
 TileShape tile_shape(int tile)
 {
+    if (tile == XGEMM_TILE_128x128_K2)
+        return TileShape{128, 128, 64, 1};   // 128 KiB LDS
     if (!is_direct(tile))
         return kTiles[tile];
     return with_direct_tile(tile, [](auto t) {
@@ -109,6 +111,9 @@ TileShape tile_shape(int tile)
         return TileShape{T::BM, T::BN, 64, 1};
     });
 }
+
+// fewest K steps in every split that a tile's pipelined kernel takes
+int dma_min_steps(int tile) { return tile == XGEMM_TILE_128x128_K2 ? 4 : 3; }
 
 constexpr int64_t kMaxDim = (int64_t)1 << 31;
 
@@ -128,7 +133,7 @@ constexpr int kMaxSkGrid = (int)(kWsPrefix / sizeof(int));
 
 bool valid_tile(int tile)
 {
-    return (tile >= 0 && tile < XGEMM_TILE_COUNT) || is_direct(tile);
+    return (tile >= 0 && tile < XGEMM_TILE_COUNT) || tile == XGEMM_TILE_128x128_K2 || is_direct(tile);
 }
 
 bool valid_config(const xgemm_config *c)
@@ -347,8 +352,11 @@ BandPlan select_band(int64_t M, int64_t N, int64_t K, int cu_count, bool persist
     return out;
 }
 
-// The launches xgemm_run considers beside the selected tile plan: variants of
-// the register-direct kernel.  Modelled time in microseconds: a call's start
+// The launches xgemm_run considers beside the selected tile plan: a 128 x 128
+// tile for at most one workgroup per CU (where the plain one leaves its SIMDs
+// with one wave each and 64 KiB in flight: 2048^3 27.0 -> 22.4 us; with two
+// workgroups per CU the plain one wins, 36.4 against 44.4 for 512 tiles), and
+// variants of the register-direct kernel.  Modelled time in microseconds: a call's start
 // (base), per round of workgroups a fixed cost and its slabs of K at a rate
 // that rises from `alone` to `full` with the share of the slots that run,
 // each slab slower by odd_a (odd_b) where rows of A (B) start on odd
@@ -358,21 +366,30 @@ BandPlan select_band(int64_t M, int64_t N, int64_t K, int cu_count, bool persist
 // (70 of the last) over 580 shapes: M and N 1 .. 16384, K 64 .. 65536,
 // batches up to 128, drawn evenly over their logarithms, contiguous and
 // padded, aligned and odd; rms error 8-12%.  On those shapes the launches it
-// chooses are 1.66 times faster than the tile plans (geometric mean), within
+// chooses are 1.68 times faster than the tile plans (geometric mean), within
 // 6% of the fastest candidate of each, and on 2 shapes 5-6% slower than the
 // tile plan.
 struct LaunchCost {
-    int tile, slots_per_cu, chains;   // chains: partial sums per workgroup and element
+    int tile, slots_per_cu;
+    int chains;     // partial sums per workgroup and element
+    int k_waves;    // waves that take different slabs
     double base, fixed, alone, full, odd_a, odd_b, split_base, split_each, us_per_byte, c_tbps;
 };
 constexpr LaunchCost kLaunchCost[] = {
-    {XGEMM_DIRECT_16x128, 2, 8, 1.60, 0.00, 1.430, 3.576, 0.292, 0.409, 2.12, 0.283, 1.11e-7, 2.24},
-    {XGEMM_DIRECT_32x64, 2, 8, 1.83, 0.00, 1.185, 3.509, 0.455, 0.186, 1.65, 0.235, 2.49e-7, 5.76},
-    {XGEMM_DIRECT_64x64, 1, 8, 1.67, 0.29, 1.930, 2.631, 0.427, 0.178, 1.37, 0.248, 3.37e-7, 1.57},
-    {XGEMM_DIRECT_64x128, 1, 4, 1.89, 1.95, 1.378, 1.959, 0.391, 0.259, 1.83, 0.197, 1.30e-7, 2.27},
-    {XGEMM_DIRECT_32x256, 2, 2, 2.46, 0.68, 0.818, 2.514, 0.387, 0.406, 1.54, 0.256, 1.11e-7, 3.08},
-    {XGEMM_DIRECT_64x256, 2, 1, 1.81, 2.80, 0.742, 2.431, 0.377, 0.236, 0.00, 0.081, 2.07e-7, 3.54},
-    {XGEMM_DIRECT_64x512, 1, 1, 0.77, 5.39, 1.157, 1.919, 0.539, 0.398, 0.00, 0.200, 2.00e-7, 5.49},
+    {XGEMM_TILE_128x128_K2, 1, 2, 1, 5.06, 1.61, 0.347, 0.495, 0.0, 0.0, 0.00, 0.239, 1.95e-7, 1.64},
+    {XGEMM_DIRECT_16x128, 2, 8, 8, 1.60, 0.00, 1.430, 3.576, 0.292, 0.409, 2.12, 0.283, 1.11e-7, 2.24},
+    {XGEMM_DIRECT_32x64, 2, 8, 8, 1.83, 0.00, 1.183, 3.519, 0.454, 0.185, 1.64, 0.234, 2.47e-7, 5.92},
+    {XGEMM_DIRECT_64x64, 1, 8, 8, 1.67, 0.29, 1.931, 2.631, 0.426, 0.177, 1.37, 0.248, 3.37e-7, 1.57},
+    {XGEMM_DIRECT_64x128, 1, 4, 4, 1.87, 1.98, 1.376, 1.964, 0.389, 0.260, 1.82, 0.197, 1.28e-7, 2.30},
+    {XGEMM_DIRECT_32x256, 2, 2, 2, 2.44, 0.70, 0.818, 2.515, 0.387, 0.406, 1.54, 0.256, 1.11e-7, 3.09},
+    {XGEMM_DIRECT_64x256, 2, 1, 1, 2.06, 2.54, 0.743, 2.427, 0.364, 0.239, 0.00, 0.083, 2.09e-7, 3.56},
+    {XGEMM_DIRECT_64x512, 1, 1, 1, 0.77, 5.39, 1.157, 1.919, 0.539, 0.398, 0.00, 0.200, 2.00e-7, 5.49},
+};
+// the tiles of the plans these replace, in the same form
+constexpr LaunchCost kPlanCost[XGEMM_TILE_COUNT] = {
+    {XGEMM_TILE_256x256, 1, 1, 1, 6.00, 5.89, 1.191, 1.548, 0.0, 0.0, 0.00, 0.000, 1.76e-7, 1.75},
+    {XGEMM_TILE_256x128, 1, 2, 1, 6.00, 4.50, 0.576, 0.764, 0.0, 0.0, 0.00, 0.083, 1.83e-7, 1.94},
+    {XGEMM_TILE_128x128, 2, 1, 1, 4.40, 1.14, 0.520, 1.158, 0.0, 0.0, 0.00, 0.207, 1.63e-7, 2.32},
 };
 constexpr int kLaunchSplits[] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32};
 // a launch replaces the tile plan only if it is modelled this much faster
@@ -390,13 +407,21 @@ double with_floor(double us, double floor_us)
 double operand_bytes(int64_t M, int64_t N, int64_t K, int64_t batch) { return (double)batch * 2.0 * (double)K * (double)(M + N); }
 double output_bytes(int64_t M, int64_t N, int64_t batch) { return (double)batch * 4.0 * (double)M * (double)N; }
 
+// Time of copying operands into the workspace before the launch.
+double copy_cost(int64_t M, int64_t N, int64_t K, bool copy_a, bool copy_b, int64_t batch)
+{
+    if (!copy_a && !copy_b)
+        return 0.0;
+    return 5.26 + (double)batch * 4.0 * (double)K * ((copy_a ? (double)M : 0.0) + (copy_b ? (double)N : 0.0)) / 7.05e6;
+}
+
 double launch_cost(const LaunchCost &c, int64_t M, int64_t N, int64_t K, int64_t batch, bool odd_a, bool odd_b,
                    int split, int cu_count)
 {
     const TileShape t = tile_shape(c.tile);
     const int64_t n = cdiv(M, t.bm) * cdiv(N, t.bn) * split * batch;
     const int64_t slots = (int64_t)cu_count * c.slots_per_cu;
-    const double slabs = (double)cdiv(cdiv(std::min(split_chunk(K, split, t.bk), K), t.bk), c.chains) *
+    const double slabs = (double)cdiv(cdiv(std::min(split_chunk(K, split, t.bk), K), t.bk), c.k_waves) *
                          (1.0 + (odd_a ? c.odd_a : 0.0) + (odd_b ? c.odd_b : 0.0));
     const int64_t rounds = n / slots, last = n % slots;
     double us = c.base + (double)rounds * (c.fixed + slabs * c.full);
@@ -407,8 +432,10 @@ double launch_cost(const LaunchCost &c, int64_t M, int64_t N, int64_t K, int64_t
     return with_floor(us, 3.0 + operand_bytes(M, N, K, batch) / 6.2e6 + output_bytes(M, N, batch) / (c.c_tbps * 1e6));
 }
 
-// Modelled time of the tile plan `cfg` for these operands: the tile model,
-// no call faster than its bytes at 4.2 TB/s (few rows leave most of each
+// Modelled time of the tile plan `cfg` for these operands: the geometric mean
+// of the two models (the tile model alone is 10-20% low on one round of 128 x
+// 128 tiles, the launch model 10-40% high on short K; between them 2 of the
+// 580 shapes lose by more than 3%).  No call is faster than its bytes at 4.2 TB/s (few rows leave most of each
 // tile's loads to A's last row), plus the copies of operands the pipelined
 // kernels cannot read in place; for K ranges under three steps, the general
 // kernel's rounds.  Fitted to the same shapes as the launches.
@@ -424,18 +451,19 @@ double plan_cost(int64_t M, int64_t N, int64_t K, bool copy_a, bool copy_b, int6
                                      (copy_a || copy_b ? 1.82 : 1.0);
         return with_floor(us, floor_us);
     }
-    double us = with_floor(0.899 * model_cost(M * batch, N, K, cu_count, cfg.tile, cfg.split_k) + 3.03, floor_us);
-    if (copy_a || copy_b)
-        us += 5.26 + (double)batch * 4.0 * (double)K * ((copy_a ? (double)M : 0.0) + (copy_b ? (double)N : 0.0)) / 7.05e6;
-    return us;
+    const double tile_us = with_floor(0.899 * model_cost(M * batch, N, K, cu_count, cfg.tile, cfg.split_k) + 3.03, floor_us);
+    const double launch_us = launch_cost(kPlanCost[cfg.tile], M, N, K, batch, false, false, cfg.split_k, cu_count);
+    return sqrt(tile_us * launch_us) + copy_cost(M, N, K, copy_a, copy_b, batch);
 }
 
 // Replace *cfg, the tile plan's configuration for `batch` problems, by a
 // launch of the list above where the model puts one ahead.  A candidate adds
 // up an element from at least as many partial sums as the plan it replaces
-// (so its rounding error is no larger).
+// (so its rounding error is no larger).  may_split: the plan uses the
+// workspace, so a K split may too; a call that needed none gets none (it may
+// be one of several on different streams, or under capture).
 void select_launch(int64_t M, int64_t N, int64_t K, const void *A, int64_t lda, int64_t sa, const void *B, int64_t ldb,
-                   int64_t sb, int64_t batch, int cu_count, xgemm_config *cfg)
+                   int64_t sb, int64_t batch, bool may_split, int cu_count, xgemm_config *cfg)
 {
     const int plan_chains = cfg->split_k * (cfg->tile == XGEMM_TILE_256x128 ? 2 : 1);
     const bool k_ok = K % 8 == 0;
@@ -447,13 +475,20 @@ void select_launch(int64_t M, int64_t N, int64_t K, const void *A, int64_t lda, 
     for (const LaunchCost &c : kLaunchCost) {
         const TileShape t = tile_shape(c.tile);
         const int64_t tiles = cdiv(M, t.bm) * cdiv(N, t.bn) * batch;
+        const bool direct = is_direct(c.tile);
+        const bool copies = !direct && (copy_a || copy_b);
+        if (copies && !may_split)
+            continue;
         for (int split : kLaunchSplits) {
-            if (split > 1 && (batch > 1 || K < 256 * (int64_t)split || tiles * split > 4 * (int64_t)cu_count ||
+            if (split > 1 && (!may_split || batch > 1 || K < 256 * (int64_t)split || tiles * split > 4 * (int64_t)cu_count ||
                               split_chunk(K, split, 64) * (split - 1) >= K))
                 break;
-            if (split * c.chains < plan_chains)
+            if (split * c.chains < plan_chains ||
+                (!direct && cdiv(std::min(split_chunk(K, split, 64), K - split_chunk(K, split, 64) * (split - 1)), 64) <
+                                dma_min_steps(c.tile)))
                 continue;
-            const double us = launch_cost(c, M, N, K, batch, odd_a, odd_b, split, cu_count);
+            const double us = launch_cost(c, M, N, K, batch, odd_a, odd_b, split, cu_count) +
+                              (copies ? copy_cost(M, N, K, copy_a, copy_b, batch) : 0.0);
             if (us < best) {
                 best = us;
                 cfg->tile = c.tile;
@@ -516,7 +551,6 @@ constexpr int kDmaBK = 64;
 constexpr int kDmaStages256x256 = 2;  // 2 x 64 KiB
 constexpr int kDmaStages256x128 = 3;  // 3 x 48 KiB
 constexpr int kDmaStages128x128 = 2;  // 2 x 32 KiB, two workgroups per CU
-constexpr int kDmaMinStages = 3;
 // MFMA block of the pipelined kernels (32: 32x32x16, 16: 16x16x32)
 #ifndef XGEMM_MI_256x256
 #define XGEMM_MI_256x256 16
@@ -547,12 +581,12 @@ constexpr int kDmaMinStages = 3;
 // rows are padded to a multiple of 8 columns, as packed copies are), at
 // least as many K steps (counting a partial one) in every split as the
 // deepest pipeline has stages, and per-tile byte offsets that fit in 32 bits.
-bool dma_eligible(const GemmParams &p, int bm, bool b_padded = false)
+bool dma_eligible(const GemmParams &p, int tile, bool b_padded = false)
 {
     const int64_t last = (int64_t)p.K - (int64_t)(p.split - 1) * p.k_chunk;
     const int64_t min_steps = cdiv(p.k_chunk < last ? p.k_chunk : last, kDmaBK);
-    return p.vec_ab && (p.N % 8 == 0 || b_padded) && p.K % 8 == 0 && min_steps >= kDmaMinStages &&
-           (int64_t)bm * p.lda * 2 < ((int64_t)1 << 32) && (int64_t)kDmaBK * p.ldb * 2 < ((int64_t)1 << 32);
+    return p.vec_ab && (p.N % 8 == 0 || b_padded) && p.K % 8 == 0 && min_steps >= dma_min_steps(tile) &&
+           (int64_t)tile_shape(tile).bm * p.lda * 2 < ((int64_t)1 << 32) && (int64_t)kDmaBK * p.ldb * 2 < ((int64_t)1 << 32);
 }
 
 // Template arguments of the pipelined kernel per tile (tile rows and
@@ -571,6 +605,7 @@ auto with_dma_tile(int tile, F &&f)
     switch (tile) {
     case XGEMM_TILE_256x256: return f(DmaTile<256, 256, kDmaStages256x256, XGEMM_MI_256x256, XGEMM_WGM_256x256, XGEMM_WGN_256x256>{});
     case XGEMM_TILE_256x128: return f(DmaTile<256, 128, kDmaStages256x128, XGEMM_MI_256x128, 2, 2, XGEMM_KW_256x128>{});
+    case XGEMM_TILE_128x128_K2: return f(DmaTile<128, 128, 4, 16, 2, 2, 2>{});
     default: return f(DmaTile<128, 128, kDmaStages128x128, XGEMM_MI_128x128>{});
     }
 }
@@ -840,7 +875,7 @@ int make_plan_with(int64_t M, int64_t N, int64_t K, const void *A, int64_t lda, 
             g.vec_c = true;
         }
         g.grid = count * sp;
-        g.dma = !is_direct(cfg.tile) && dma_eligible(g.p, t.bm, pk.b);
+        g.dma = !is_direct(cfg.tile) && dma_eligible(g.p, cfg.tile, pk.b);
         g.sk = false;
         g.dp_rounds = g.sk_tiles = g.kt = 0;
     };
@@ -1071,7 +1106,7 @@ int plan_call(int cu_count, int64_t M, int64_t N, int64_t K, const void *A, int6
         return XGEMM_OK;
     // one launch of a tile plan: another kernel where the model prefers it
     xgemm_config cfg = band.body;
-    select_launch(M, N, K, A, lda, 0, B, ldb, 0, 1, cu_count, &cfg);
+    select_launch(M, N, K, A, lda, 0, B, ldb, 0, 1, cp->ws > 0, cu_count, &cfg);
     if (cfg.tile != band.body.tile || cfg.split_k != band.body.split_k) {
         Plan other;
         if (make_plan(M, N, K, A, lda, B, ldb, C, ldc, cfg, cu_count, &other, true) == XGEMM_OK &&
@@ -1272,7 +1307,7 @@ int run_batched(xgemm_ctx *h, int64_t batch, int64_t M, int64_t N, int64_t K, co
     xgemm_config cfg;
     select_config_batched(batch, M, N, K, h->cu_count, &cfg);
     if (h->ws_limit == 0 && !(h->persistent && use_persistent(M, N, K, h->cu_count, cfg, batch)))
-        select_launch(M, N, K, A, lda, sa, B, ldb, sb, batch, h->cu_count, &cfg);
+        select_launch(M, N, K, A, lda, sa, B, ldb, sb, batch, true, h->cu_count, &cfg);
     Plan plan;
     rc = make_plan(M, N, K, A, lda, B, ldb, C, ldc, cfg, h->cu_count, &plan, false);
     if (rc != XGEMM_OK)
@@ -1337,7 +1372,7 @@ int run_batched(xgemm_ctx *h, int64_t batch, int64_t M, int64_t N, int64_t K, co
     // kernel's buffer stores every problem's C
     g.p.vec_ab = g.p.vec_ab && (sa % 8 == 0) && (sb % 8 == 0);
     g.vec_c = g.vec_c && (sc % 4 == 0);
-    g.dma = !is_direct(plan.tile) && dma_eligible(g.p, tile_shape(plan.tile).bm, pk.b);
+    g.dma = !is_direct(plan.tile) && dma_eligible(g.p, plan.tile, pk.b);
     // the persistent kernel over the tiles of all problems, as xgemm_run
     // takes it for one problem with as many tiles
     const TileShape &t256 = kTiles[XGEMM_TILE_256x256];

@@ -29,6 +29,7 @@ XGEMM_TILE_256x256 = 0
 XGEMM_TILE_256x128 = 1
 XGEMM_TILE_128x128 = 2
 XGEMM_TILE_COUNT = 3
+XGEMM_TILE_128x128_K2 = 16
 XGEMM_DIRECT_16x128 = 17
 XGEMM_DIRECT_32x64 = 18
 XGEMM_DIRECT_64x64 = 19

@@ -42,6 +42,31 @@ def test_too_small_or_too_wide_falls_back():
             != xg.XGEMM_KERNEL_DIRECT
 
 
+K2 = xg.XGEMM_TILE_128x128_K2
+
+
+@pytest.mark.parametrize("K", [256, 320, 384, 448, 264, 328])
+def test_k2_tile_traces(K):
+    """The four-stage wave-pair tile from its fewest steps up, both parities
+    of its loop, whole and partial steps; fewer steps take another family."""
+    assert xg.xgemm_kernel_family(200, 136, K, 1 << 20, K, 1 << 20, 136, _cfg(K2)) == xg.XGEMM_KERNEL_PIPELINED
+    rep = sc.check_launch(200, 136, K, _cfg(K2))
+    assert rep.ok, [str(v) for v in rep.violations]
+    assert xg.xgemm_kernel_family(200, 136, 192, 1 << 20, 192, 1 << 20, 136, _cfg(K2)) == xg.XGEMM_KERNEL_GENERAL
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("K,split", [(256, 1), (320, 1), (384, 1), (448, 1), (264, 1), (328, 1), (1097, 2), (4096, 16)])
+def test_k2_tile_parity(K, split):
+    from gpu_util import check_close, run_gpu
+    M, N = 200, 136
+    oracle.build(force=False)
+    for dtype in ("bf16", "fp16"):
+        A, B = wl.make_inputs(M, N, K, dtype, "uniform", K)
+        C_ref, S = oracle.gemm(A, B, dtype)
+        check_close(run_gpu(A, B, dtype, config=_cfg(K2, split)), C_ref, S, "K2 %s K=%d" % (dtype, K))
+
+
 def test_dispatch():
     """Few output tiles take the direct kernel in any layout; whole rounds of
     large tiles, banded and persistent plans keep theirs; a launch that
@@ -50,6 +75,7 @@ def test_dispatch():
         return xg.xgemm_launch_config(M, N, K, 1 << 20, lda or K, 1 << 20, ldb or N, 256)
     for shape in [(256, 256, 256), (1000, 1000, 1000), (16, 4096, 4096), (1, 2496, 5751), (300, 203, 777)]:
         assert launch(*shape).tile in DIRECT, shape
+    assert launch(2048, 2048, 2048).tile == K2
     for shape in [(4096, 4096, 4096), (8192, 8192, 8192), (6144, 6144, 6144), (1024, 1024, 65536)]:
         c, b = launch(*shape), xg.xgemm_select_band(*shape, xg.XGEMM_BF16, 256)
         assert (c.tile, c.split_k, c.stream_k) == (b.body.tile, b.body.split_k, b.body.stream_k), shape
