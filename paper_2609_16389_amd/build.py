@@ -1,4 +1,5 @@
-"""Build libxgemm.so (the HIP library behind include/xgemm.h) for gfx950, in-tree."""
+"""Build libxgemm.so (the HIP library behind include/xgemm.h) for gfx950 and
+_fastcall.so (its calls from Python), in-tree."""
 from __future__ import annotations
 
 import os
@@ -11,6 +12,8 @@ DEPS = [SRC, os.path.join(PKG, "csrc", "direct_kernel.hpp"), os.path.join(PKG, "
         os.path.join(PKG, "csrc", "pack_kernel.hpp"), os.path.join(PKG, "csrc", "sk_kernel.hpp"),
         os.path.join(ROOT, "include", "xgemm.h")]
 LIB = os.path.join(PKG, "libxgemm.so")
+FAST_SRC = os.path.join(PKG, "csrc", "fastcall.cpp")
+FAST_LIB = os.path.join(PKG, "_fastcall.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 # Packed fp32 vector ops are disabled for all device code.
@@ -27,14 +30,34 @@ def build(verbose: bool = False) -> str:
         print(" ".join(cmd), flush=True)
     subprocess.run(cmd, check=True)
     os.replace(tmp, LIB)
+    build_fastcall(verbose)
     return LIB
 
 
+def build_fastcall(verbose: bool = False) -> str:
+    """Compile the Python extension against torch's headers (host code only)."""
+    import sysconfig
+
+    import torch
+    root = os.path.dirname(torch.__file__)
+    tmp = FAST_LIB + ".tmp%d" % os.getpid()
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__=1",
+           "-DUSE_ROCM=1", "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI,
+           "-I" + os.path.join(root, "include"), "-I" + os.path.join(root, "include", "torch", "csrc", "api", "include"),
+           "-I" + sysconfig.get_paths()["include"], "-I/opt/rocm/include", FAST_SRC, "-o", tmp,
+           "-L" + os.path.join(root, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.run(cmd, check=True)
+    os.replace(tmp, FAST_LIB)
+    return FAST_LIB
+
+
 def is_stale() -> bool:
-    if not os.path.exists(LIB):
+    if not os.path.exists(LIB) or not os.path.exists(FAST_LIB):
         return True
     t = os.path.getmtime(LIB)
-    return any(os.path.getmtime(d) > t for d in DEPS)
+    return any(os.path.getmtime(d) > t for d in DEPS) or os.path.getmtime(FAST_SRC) > os.path.getmtime(FAST_LIB)
 
 
 if __name__ == "__main__":

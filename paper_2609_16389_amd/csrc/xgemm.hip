@@ -59,6 +59,7 @@ struct xgemm_ctx {
     size_t ws_limit;        // largest workspace the handle may allocate (0: no limit)
     bool persistent;        // the selected plans may use the persistent kernel
     void *scratch;          // this device's `scratch` array (xgemm_run_noalloc)
+    struct PlanCache *plans;  // selections already made (sizes and layout flags only)
     char last_error[256];
 };
 
@@ -352,6 +353,47 @@ BandPlan select_band(int64_t M, int64_t N, int64_t K, int cu_count, bool persist
     return out;
 }
 
+}  // namespace
+
+// Selections a handle has made, by what they depend on: sizes and layout
+// flags (no address).  Evaluating the models takes 0.5 to 6 us of host time
+// per call, as long as a small product runs; programs repeat few shapes.
+// Direct-mapped and of fixed size; a handle is used by one host thread at a
+// time, so nothing is locked.
+struct PlanCache {
+    static constexpr int kSlots = 128;
+    struct Band {
+        int64_t M = -1, N = 0, K = 0;
+        int persistent = 0;
+        BandPlan plan;
+    } band[kSlots];
+    struct Launch {
+        int64_t M = -1, N = 0, K = 0, batch = 0;
+        int flags = 0;
+        xgemm_config from{}, to{};
+    } launch[kSlots];
+    static int slot(int64_t M, int64_t N, int64_t K)
+    {
+        const uint64_t x = ((uint64_t)M * 0x9E3779B97F4A7C15ull) ^ ((uint64_t)N * 0xC2B2AE3D27D4EB4Full) ^
+                           ((uint64_t)K * 0x165667B19E3779F9ull);
+        return (int)(x >> 57);
+    }
+};
+
+namespace {
+
+BandPlan cached_band(PlanCache *cache, int64_t M, int64_t N, int64_t K, int cu_count, bool persistent)
+{
+    if (!cache)
+        return select_band(M, N, K, cu_count, persistent);
+    PlanCache::Band &e = cache->band[PlanCache::slot(M, N, K)];
+    if (e.M != M || e.N != N || e.K != K || e.persistent != (int)persistent) {
+        e.plan = select_band(M, N, K, cu_count, persistent);
+        e.M = M, e.N = N, e.K = K, e.persistent = (int)persistent;
+    }
+    return e.plan;
+}
+
 // The launches xgemm_run considers beside the selected tile plan: a 128 x 128
 // tile for at most one workgroup per CU (where the plain one leaves its SIMDs
 // with one wave each and 64 KiB in flight: 2048^3 27.0 -> 22.4 us; with two
@@ -463,7 +505,7 @@ double plan_cost(int64_t M, int64_t N, int64_t K, bool copy_a, bool copy_b, int6
 // workspace, so a K split may too; a call that needed none gets none (it may
 // be one of several on different streams, or under capture).
 void select_launch(int64_t M, int64_t N, int64_t K, const void *A, int64_t lda, int64_t sa, const void *B, int64_t ldb,
-                   int64_t sb, int64_t batch, bool may_split, int cu_count, xgemm_config *cfg)
+                   int64_t sb, int64_t batch, bool may_split, int cu_count, PlanCache *cache, xgemm_config *cfg)
 {
     const int plan_chains = cfg->split_k * (cfg->tile == XGEMM_TILE_256x128 ? 2 : 1);
     const bool k_ok = K % 8 == 0;
@@ -471,6 +513,14 @@ void select_launch(int64_t M, int64_t N, int64_t K, const void *A, int64_t lda, 
     const bool copy_b = !(k_ok && (uintptr_t)B % 16 == 0 && ldb % 8 == 0 && sb % 8 == 0 && N % 8 == 0);
     const bool odd_a = (uintptr_t)A % 4 != 0 || lda % 2 != 0 || sa % 2 != 0;
     const bool odd_b = (uintptr_t)B % 4 != 0 || ldb % 2 != 0 || sb % 2 != 0;
+    const int flags = copy_a | copy_b << 1 | odd_a << 2 | odd_b << 3 | may_split << 4;
+    PlanCache::Launch *const e = cache ? &cache->launch[PlanCache::slot(M, N, K)] : nullptr;
+    if (e && e->M == M && e->N == N && e->K == K && e->batch == batch && e->flags == flags &&
+        e->from.tile == cfg->tile && e->from.split_k == cfg->split_k && e->from.group_m == cfg->group_m) {
+        *cfg = e->to;
+        return;
+    }
+    const xgemm_config from = *cfg;
     double best = kLaunchMargin * plan_cost(M, N, K, copy_a, copy_b, batch, *cfg, cu_count);
     for (const LaunchCost &c : kLaunchCost) {
         const TileShape t = tile_shape(c.tile);
@@ -497,6 +547,12 @@ void select_launch(int64_t M, int64_t N, int64_t K, const void *A, int64_t lda, 
                 cfg->stream_k = 0;
             }
         }
+    }
+    if (e) {
+        e->M = M, e->N = N, e->K = K, e->batch = batch;
+        e->flags = flags;
+        e->from = from;
+        e->to = *cfg;
     }
 }
 
@@ -1058,13 +1114,14 @@ struct CallPlan {
 // is, for the caller to refuse, and another launch is taken in its place only
 // within it.  Touches no GPU.
 int plan_call(int cu_count, int64_t M, int64_t N, int64_t K, const void *A, int64_t lda, const void *B, int64_t ldb,
-              float *C, int64_t ldc, const xgemm_config *forced, CallPlan *cp, bool allow_sk = true, size_t limit = 0)
+              float *C, int64_t ldc, const xgemm_config *forced, CallPlan *cp, bool allow_sk = true, size_t limit = 0,
+              PlanCache *cache = nullptr)
 {
     BandPlan band;
     if (forced) {
         band.body = *forced;
     } else {
-        band = select_band(M, N, K, cu_count, allow_sk);
+        band = cached_band(cache, M, N, K, cu_count, allow_sk);
     }
     if (!allow_sk)
         band.body.stream_k = band.band.stream_k = 0;
@@ -1077,7 +1134,7 @@ int plan_call(int cu_count, int64_t M, int64_t N, int64_t K, const void *A, int6
         if (rc != XGEMM_OK)
             return rc;
         if (!probe.seg[0].sk)
-            band = select_band(M, N, K, cu_count, false);
+            band = cached_band(cache, M, N, K, cu_count, false);
     }
     if (band.axis == XGEMM_BAND_NONE) {
         cp->parts = 1;
@@ -1106,7 +1163,7 @@ int plan_call(int cu_count, int64_t M, int64_t N, int64_t K, const void *A, int6
         return XGEMM_OK;
     // one launch of a tile plan: another kernel where the model prefers it
     xgemm_config cfg = band.body;
-    select_launch(M, N, K, A, lda, 0, B, ldb, 0, 1, cp->ws > 0, cu_count, &cfg);
+    select_launch(M, N, K, A, lda, 0, B, ldb, 0, 1, cp->ws > 0, cu_count, cache, &cfg);
     if (cfg.tile != band.body.tile || cfg.split_k != band.body.split_k) {
         Plan other;
         if (make_plan(M, N, K, A, lda, B, ldb, C, ldc, cfg, cu_count, &other, true) == XGEMM_OK &&
@@ -1161,7 +1218,8 @@ int run(xgemm_ctx *h, int64_t M, int64_t N, int64_t K, const void *A, int64_t ld
     if (K == 0)
         return launch_zero(h, M, N, C, ldc, s);
     CallPlan cp;
-    rc = plan_call(h->cu_count, M, N, K, A, lda, B, ldb, C, ldc, forced, &cp, forced || h->persistent, h->ws_limit);
+    rc = plan_call(h->cu_count, M, N, K, A, lda, B, ldb, C, ldc, forced, &cp, forced || h->persistent, h->ws_limit,
+                   h->plans);
     if (rc != XGEMM_OK)
         return rc;
     if (cp.ws > 0 && (rc = acquire_workspace(h, cp.ws, s)) != XGEMM_OK)
@@ -1307,7 +1365,7 @@ int run_batched(xgemm_ctx *h, int64_t batch, int64_t M, int64_t N, int64_t K, co
     xgemm_config cfg;
     select_config_batched(batch, M, N, K, h->cu_count, &cfg);
     if (h->ws_limit == 0 && !(h->persistent && use_persistent(M, N, K, h->cu_count, cfg, batch)))
-        select_launch(M, N, K, A, lda, sa, B, ldb, sb, batch, true, h->cu_count, &cfg);
+        select_launch(M, N, K, A, lda, sa, B, ldb, sb, batch, true, h->cu_count, h->plans, &cfg);
     Plan plan;
     rc = make_plan(M, N, K, A, lda, B, ldb, C, ldc, cfg, h->cu_count, &plan, false);
     if (rc != XGEMM_OK)
@@ -1807,6 +1865,7 @@ int xgemm_create(xgemm_handle_t *out)
     h->persistent = true;
     h->last_error[0] = '\0';
     h->scratch = nullptr;
+    h->plans = new (std::nothrow) PlanCache;   // without it every call selects anew
     if (dev >= 0 && dev < kMaxDevices) {
         // once per device, with the device current: the address of this
         // device's copy of the scratch array
@@ -1815,6 +1874,7 @@ int xgemm_create(xgemm_handle_t *out)
             void *ptr = nullptr;
             if (hipGetSymbolAddress(&ptr, HIP_SYMBOL(scratch)) != hipSuccess || !ptr) {
                 (void)hipGetLastError();
+                delete h->plans;
                 delete h;
                 return XGEMM_ERR_HIP;
             }
@@ -1822,6 +1882,7 @@ int xgemm_create(xgemm_handle_t *out)
             if (hipMemsetAsync(ptr, 0, kWsPrefix, nullptr) != hipSuccess ||
                 hipStreamSynchronize(nullptr) != hipSuccess) {
                 (void)hipGetLastError();
+                delete h->plans;
                 delete h;
                 return XGEMM_ERR_HIP;
             }
@@ -1831,6 +1892,7 @@ int xgemm_create(xgemm_handle_t *out)
     }
     if (hipEventCreateWithFlags(&h->ws_event, hipEventDisableTiming) != hipSuccess) {
         (void)hipGetLastError();
+        delete h->plans;
         delete h;
         return XGEMM_ERR_HIP;
     }
@@ -1851,6 +1913,7 @@ int xgemm_destroy(xgemm_handle_t h)
         (void)hipGetLastError();
         rc = XGEMM_ERR_HIP;
     }
+    delete h->plans;
     delete h;
     return rc;
 }
@@ -1894,9 +1957,10 @@ int xgemm_run_noalloc(xgemm_handle_t h, int64_t M, int64_t N, int64_t K, const v
     if (K == 0)
         return launch_zero(h, M, N, C, ldc, s);
     CallPlan cp;
-    rc = plan_call(h->cu_count, M, N, K, A, lda, B, ldb, C, ldc, nullptr, &cp, h->persistent, kScratchBytes);
+    rc = plan_call(h->cu_count, M, N, K, A, lda, B, ldb, C, ldc, nullptr, &cp, h->persistent, kScratchBytes,
+                   h->plans);
     if (rc == XGEMM_OK && cp.ws + kWsPrefix > kScratchBytes)   // a persistent plan's partials may not fit
-        rc = plan_call(h->cu_count, M, N, K, A, lda, B, ldb, C, ldc, nullptr, &cp, false, kScratchBytes);
+        rc = plan_call(h->cu_count, M, N, K, A, lda, B, ldb, C, ldc, nullptr, &cp, false, kScratchBytes, h->plans);
     if (rc != XGEMM_OK)
         return rc;
     if (cp.ws + kWsPrefix > kScratchBytes) {

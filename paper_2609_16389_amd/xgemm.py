@@ -1,10 +1,13 @@
-"""ctypes binding for libxgemm (include/xgemm.h).
+"""Python binding for libxgemm (include/xgemm.h).
 
 Argument marshalling only: every entry point forwards to the HIP library with
 the same name, and all arithmetic runs in its kernels.  Torch tensors are used
 for device memory and streams; ``gemm`` reads their pointers, strides and the
-current stream and calls ``xgemm_run``.  There is no fallback path: if
-``libxgemm.so`` is missing the import of this module fails.
+current stream and calls ``xgemm_run``.  Every entry point is bound with
+ctypes; the ones on a program's hot path are called through ``_fastcall`` (the
+same library functions, without ctypes' argument conversion) when their
+arguments are of the plain kind.  There is no fallback path: if
+``libxgemm.so`` or ``_fastcall.so`` is missing the import of this module fails.
 """
 from __future__ import annotations
 
@@ -123,6 +126,8 @@ if not os.path.exists(_LIB_PATH):
 
 lib = ctypes.CDLL(_LIB_PATH)
 
+from paper_2609_16389_amd import _fastcall  # noqa: E402
+
 _i64, _i32, _p = ctypes.c_int64, ctypes.c_int, ctypes.c_void_p
 _handle_t = ctypes.c_void_p
 
@@ -212,11 +217,13 @@ def xgemm_set_persistent(h, enable) -> int:
 
 
 def xgemm_run(h, M, N, K, A, lda, B, ldb, C, ldc, dtype, stream) -> int:
-    return lib.xgemm_run(h, M, N, K, A, lda, B, ldb, C, ldc, dtype, stream)
+    rc = _fastcall.run(h, M, N, K, A, lda, B, ldb, C, ldc, dtype, stream)
+    return lib.xgemm_run(h, M, N, K, A, lda, B, ldb, C, ldc, dtype, stream) if rc is None else rc
 
 
 def xgemm_run_noalloc(h, M, N, K, A, lda, B, ldb, C, ldc, dtype, stream) -> int:
-    return lib.xgemm_run_noalloc(h, M, N, K, A, lda, B, ldb, C, ldc, dtype, stream)
+    rc = _fastcall.run_noalloc(h, M, N, K, A, lda, B, ldb, C, ldc, dtype, stream)
+    return lib.xgemm_run_noalloc(h, M, N, K, A, lda, B, ldb, C, ldc, dtype, stream) if rc is None else rc
 
 
 XGEMM_NOALLOC_SCRATCH_BYTES = 64 << 20
@@ -355,6 +362,16 @@ def xgemm_last_error(h) -> str:
 
 _handles = {}
 
+_fastcall.bind(*(ctypes.cast(f, ctypes.c_void_p).value for f in
+                 (lib.xgemm_run, lib.xgemm_run_noalloc, lib.xgemm_run_strided_batched, lib.xgemv_run)), _handles)
+
+
+def _checked(rc, device_index, out):
+    """``out`` once a fast call on torch's current stream has succeeded."""
+    if rc != XGEMM_OK:
+        raise XgemmError(rc, xgemm_last_error(handle(device_index, torch.cuda.current_stream(device_index))))
+    return out
+
 
 def _stream_ptr(stream) -> int:
     """The hipStream_t address of a torch stream, a raw address or None (the
@@ -410,7 +427,10 @@ def bmm(A, B, out=None, stream=None):
     batch stride, including 0 for a broadcast operand); out: optional (L, M, N)
     float32 tensor with contiguous rows.
     """
-    import torch
+    if out is not None and stream is None:
+        rc = _fastcall.bmm(A, B, out)
+        if rc is not None:
+            return _checked(rc, A.device.index, out)
     if A.dim() != 3 or B.dim() != 3 or A.shape[0] != B.shape[0] or A.shape[2] != B.shape[1]:
         raise ValueError("expected A (L, M, K) and B (L, K, N)")
     if A.dtype != B.dtype:
@@ -445,7 +465,10 @@ def gemm(A, B, out=None, config: xgemm_config | None = None, stream=None):
     contiguous rows; out: optional (M, N) float32 tensor with contiguous rows.
     Enqueued on ``stream`` (default: torch's current stream).
     """
-    import torch
+    if out is not None and config is None and stream is None:
+        rc = _fastcall.gemm(A, B, out)
+        if rc is not None:
+            return _checked(rc, A.device.index, out)
     if A.dtype != B.dtype:
         raise TypeError("A and B must have the same dtype")
     dtype = _dtype_code(A)
@@ -476,6 +499,10 @@ def gemv(A, x, out=None, config: xgemv_config | None = None, stream=None):
     """y = A @ x for a float32 CUDA matrix A (M x K, unit column stride) and
     vector x (K, contiguous); returns y (M, float32), written into ``out`` if
     given.  Runs xgemv_run (or xgemv_run_config) on the current stream."""
+    if out is not None and config is None and stream is None:
+        rc = _fastcall.gemv(A, x, out)
+        if rc is not None:
+            return _checked(rc, A.device.index, out)
     if A.dtype != torch.float32 or x.dtype != torch.float32:
         raise TypeError("gemv takes float32 A and x")
     if A.dim() != 2 or x.dim() != 1 or A.shape[1] != x.shape[0]:
