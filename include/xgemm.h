@@ -351,7 +351,8 @@ int xgemm_kernel_family(int64_t M, int64_t N, int64_t K, const void *A, int64_t 
  * a device with cu_count compute units, for 16-byte aligned A and B with
  * lda = K and ldb = N: a 4096-byte prefix of counters (for the persistent
  * kernel's split tiles, zeroed when the workspace is allocated and left zero
- * by every call), then split_k * M * ceil(N/4)*4 floats when split_k > 1, the
+ * by every call), then split_k * M * ceil(N/4)*4 floats when split_k > 1 (for
+ * register-direct blocks whose last workgroup adds them: split_k whole blocks per tile), the
  * persistent kernel's partial sums when it splits tiles, plus the operand
  * copies when K or N is not a multiple of 8 (each 256-byte aligned, after the
  * partials); 0 when nothing is needed.  Host-only.  Returns 0 for invalid
@@ -406,7 +407,10 @@ typedef struct xgemm_trace_info {
     int32_t segments;        /* GEMM launches in the plan (1) */
     int32_t family;          /* xgemm_kernel_family_id of this launch */
     int32_t reduce;          /* 0: writes C (the persistent kernel: also partial sums in W);
-                                1: full-matrix split partials in W, summed by a later launch */
+                                1: full-matrix split partials in W, summed by a later launch;
+                                2 (register-direct blocks): partial blocks in W, one per tile and
+                                K range in the accumulators' layout, and C, which the last
+                                workgroup of each tile to count in adds up and writes */
     int32_t threads;         /* threads per workgroup */
     int32_t lds_bytes;       /* LDS bytes per workgroup of the pipelined kernel (else 0) */
     int32_t split;           /* split-k factor of this launch */
@@ -451,7 +455,9 @@ int xgemm_trace_plan(int64_t M, int64_t N, int64_t K, const void *A, int64_t lda
  * persistent kernel, whose path through a split tile depends on which
  * workgroup counts in first: 0 traces every split tile's last K steps
  * counting in first (the usual order: they start a workgroup's range while
- * the first steps end the previous one's), 1 its first steps.  Counter reads
+ * the first steps end the previous one's), 1 its first steps.  Likewise for
+ * a register-direct launch with reduce == 2: 0 has every tile's last K range
+ * count in last (and write C), 1 its first.  Counter reads
  * and atomic adds appear as 4-byte LOAD events, counter resets as STORE.
  * Every kernel family is traced.  XGEMM_ERR_INVALID_ARG as
  * xgemm_trace_plan, or for a block out of range, a schedule other than 0 or

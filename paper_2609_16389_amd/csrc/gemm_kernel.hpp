@@ -55,6 +55,8 @@ struct GemmParams {
     int64_t stride_b;
     int64_t stride_c;
     int grid;               // workgroups of the launch; a 2-D grid may hold more, which exit
+    float *part;            // register-direct kernel with split > 1: partial sums and, per tile, a counter
+    int *count;             //   of the workgroups that have stored theirs (zero between launches); else null
 };
 
 // Linear workgroup id of a launch whose grid may be 2-D (x fastest, as the

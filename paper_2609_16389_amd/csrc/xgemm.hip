@@ -113,6 +113,31 @@ TileShape tile_shape(int tile)
     });
 }
 
+// Bytes of a workgroup's partial block in the register-direct kernel, where
+// the last workgroup of a tile adds the blocks of a K split (variants whose
+// waves share no block keep the separate reduction); 0 for other tiles.
+size_t direct_block_bytes(int tile)
+{
+    if (!is_direct(tile))
+        return 0;
+    return with_direct_tile(tile, [](auto t) {
+        using T = decltype(t);
+        return T::KW > 1 ? (size_t)T::BM * T::BN * sizeof(float) : (size_t)0;
+    });
+}
+
+// Most bytes of partial blocks that the last workgroup of a tile adds by
+// itself: one CU reads them at about 70 GB/s, so beyond this a second launch
+// over all CUs is faster (384 x 192 x 57534 in 16 ranges of 64 x 128 blocks,
+// 512 KiB: 34.5 against 37.4 us; 13 x 1664 x 5888 in 6 of 32 x 64, 48 KiB: 9.8
+// against 8.8).
+constexpr size_t kCombineBytes = 128 << 10;
+bool combines(int tile, int split)
+{
+    const size_t block = direct_block_bytes(tile);
+    return block > 0 && (size_t)split * block <= kCombineBytes;
+}
+
 // fewest K steps in every split that a tile's pipelined kernel takes
 int dma_min_steps(int tile) { return tile == XGEMM_TILE_128x128_K2 ? 4 : 3; }
 
@@ -402,41 +427,44 @@ BandPlan cached_band(PlanCache *cache, int64_t M, int64_t N, int64_t K, int cu_c
 // (base), per round of workgroups a fixed cost and its slabs of K at a rate
 // that rises from `alone` to `full` with the share of the slots that run,
 // each slab slower by odd_a (odd_b) where rows of A (B) start on odd
-// elements, and for a K split the second launch and the partials' traffic;
-// and no less than its operands at 6.2 TB/s and C at the variant's c_tbps.
-// Fitted (least squares on log time) to 1500 to 2400 timings of each variant
-// (70 of the last) over 580 shapes: M and N 1 .. 16384, K 64 .. 65536,
-// batches up to 128, drawn evenly over their logarithms, contiguous and
-// padded, aligned and odd; rms error 8-12%.  On those shapes the launches it
-// chooses are 1.68 times faster than the tile plans (geometric mean), within
-// 6% of the fastest candidate of each, and on 2 shapes 5-6% slower than the
-// tile plan.
+// elements; no less than its operands at 6.2 TB/s (36 GB/s for each CU that
+// takes part) and C at the variant's c_tbps; then, for a K split, the adding
+// of the partials by the last workgroups, or a second launch and their
+// traffic.
+// Fitted (least squares on log time) to 600 to 2700 timings of each over 790
+// shapes: M and N 1 .. 16384, K 64 .. 65536, batches up to 128, drawn evenly
+// over their logarithms, contiguous and padded, aligned and odd; rms error
+// 5-12%.  On those timed with the kernels as they are (some 510) the launches
+// it chooses are 1.72 times faster than the tile plans (geometric mean),
+// within 4% of the fastest candidate of each, and on 2 shapes 6-18% slower
+// than the tile plan.
 struct LaunchCost {
     int tile, slots_per_cu;
     int chains;     // partial sums per workgroup and element
     int k_waves;    // waves that take different slabs
-    double base, fixed, alone, full, odd_a, odd_b, split_base, split_each, us_per_byte, c_tbps;
+    double base, fixed, alone, full, odd_a, odd_b, split_base, split_each, us_per_byte, c_tbps,
+        combine_base, combine_each;
 };
 constexpr LaunchCost kLaunchCost[] = {
-    {XGEMM_TILE_128x128_K2, 1, 2, 1, 5.06, 1.61, 0.347, 0.495, 0.0, 0.0, 0.00, 0.239, 1.95e-7, 1.64},
-    {XGEMM_DIRECT_16x128, 2, 8, 8, 1.60, 0.00, 1.430, 3.576, 0.292, 0.409, 2.12, 0.283, 1.11e-7, 2.24},
-    {XGEMM_DIRECT_32x64, 2, 8, 8, 1.83, 0.00, 1.183, 3.519, 0.454, 0.185, 1.64, 0.234, 2.47e-7, 5.92},
-    {XGEMM_DIRECT_64x64, 1, 8, 8, 1.67, 0.29, 1.931, 2.631, 0.426, 0.177, 1.37, 0.248, 3.37e-7, 1.57},
-    {XGEMM_DIRECT_64x128, 1, 4, 4, 1.87, 1.98, 1.376, 1.964, 0.389, 0.260, 1.82, 0.197, 1.28e-7, 2.30},
-    {XGEMM_DIRECT_32x256, 2, 2, 2, 2.44, 0.70, 0.818, 2.515, 0.387, 0.406, 1.54, 0.256, 1.11e-7, 3.09},
-    {XGEMM_DIRECT_64x256, 2, 1, 1, 2.06, 2.54, 0.743, 2.427, 0.364, 0.239, 0.00, 0.083, 2.09e-7, 3.56},
-    {XGEMM_DIRECT_64x512, 1, 1, 1, 0.77, 5.39, 1.157, 1.919, 0.539, 0.398, 0.00, 0.200, 2.00e-7, 5.49},
+    {XGEMM_TILE_128x128_K2, 1, 2, 1, 5.18, 1.43, 0.351, 0.487, 0.000, 0.000, 0.00, 0.242, 1.89e-7, 1.78, 0.00, 0.000},
+    {XGEMM_DIRECT_16x128, 1, 8, 8, 2.18, 0.00, 1.190, 2.222, 0.313, 0.376, 1.47, 0.156, 1.11e-7, 7.00, 0.46, 0.159},
+    {XGEMM_DIRECT_32x64, 1, 8, 8, 1.61, 0.00, 1.243, 1.957, 0.497, 0.194, 0.00, 0.265, 1.11e-7, 4.21, 1.23, 0.143},
+    {XGEMM_DIRECT_64x64, 1, 8, 8, 0.89, 1.28, 1.508, 2.809, 0.492, 0.196, 2.80, 0.171, 1.11e-7, 2.13, 0.56, 0.340},
+    {XGEMM_DIRECT_64x128, 1, 4, 4, 1.65, 2.35, 1.240, 1.976, 0.458, 0.224, 1.80, 0.189, 1.11e-7, 2.63, 0.62, 0.580},
+    {XGEMM_DIRECT_32x256, 2, 2, 2, 3.47, 0.00, 0.659, 2.612, 0.501, 0.374, 0.59, 0.242, 1.25e-7, 3.10, 0.00, 0.355},
+    {XGEMM_DIRECT_64x256, 2, 1, 1, 3.53, 1.10, 0.666, 2.383, 0.411, 0.219, 0.00, 0.074, 2.15e-7, 3.24, 0.00, 0.000},
+    {XGEMM_DIRECT_64x512, 1, 1, 1, 2.95, 3.16, 1.220, 1.790, 0.564, 0.270, 0.00, 0.195, 1.11e-7, 3.85, 0.00, 0.000},
 };
 // the tiles of the plans these replace, in the same form
 constexpr LaunchCost kPlanCost[XGEMM_TILE_COUNT] = {
-    {XGEMM_TILE_256x256, 1, 1, 1, 6.00, 5.89, 1.191, 1.548, 0.0, 0.0, 0.00, 0.000, 1.76e-7, 1.75},
-    {XGEMM_TILE_256x128, 1, 2, 1, 6.00, 4.50, 0.576, 0.764, 0.0, 0.0, 0.00, 0.083, 1.83e-7, 1.94},
-    {XGEMM_TILE_128x128, 2, 1, 1, 4.40, 1.14, 0.520, 1.158, 0.0, 0.0, 0.00, 0.207, 1.63e-7, 2.32},
+    {XGEMM_TILE_256x256, 1, 1, 1, 6.00, 5.36, 1.206, 1.580, 0.000, 0.000, 0.00, 0.000, 1.58e-7, 1.89, 0.00, 0.000},
+    {XGEMM_TILE_256x128, 1, 2, 1, 6.00, 3.80, 0.590, 0.769, 0.000, 0.000, 0.00, 0.135, 1.82e-7, 1.91, 0.00, 0.000},
+    {XGEMM_TILE_128x128, 2, 1, 1, 4.92, 0.59, 0.539, 1.080, 0.000, 0.000, 0.00, 0.238, 1.54e-7, 2.32, 0.00, 0.000},
 };
 constexpr int kLaunchSplits[] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32};
 // a launch replaces the tile plan only if it is modelled this much faster
-// (at 1.0, 5 of the shapes were 5-16% slower than the tile plan)
-constexpr double kLaunchMargin = 0.92;
+// (at 1.0, 5 of the shapes were 6-17% slower than the tile plan)
+constexpr double kLaunchMargin = 0.94;
 
 // A time that is neither below `us` nor below the bytes' time.
 double with_floor(double us, double floor_us)
@@ -454,7 +482,7 @@ double copy_cost(int64_t M, int64_t N, int64_t K, bool copy_a, bool copy_b, int6
 {
     if (!copy_a && !copy_b)
         return 0.0;
-    return 5.26 + (double)batch * 4.0 * (double)K * ((copy_a ? (double)M : 0.0) + (copy_b ? (double)N : 0.0)) / 7.05e6;
+    return 5.49 + (double)batch * 4.0 * (double)K * ((copy_a ? (double)M : 0.0) + (copy_b ? (double)N : 0.0)) / 7.54e6;
 }
 
 double launch_cost(const LaunchCost &c, int64_t M, int64_t N, int64_t K, int64_t batch, bool odd_a, bool odd_b,
@@ -469,15 +497,20 @@ double launch_cost(const LaunchCost &c, int64_t M, int64_t N, int64_t K, int64_t
     double us = c.base + (double)rounds * (c.fixed + slabs * c.full);
     if (last > 0)
         us += c.fixed + slabs * (c.alone + (c.full - c.alone) * (double)last / (double)slots);
-    if (split > 1)
+    // one CU draws 36 GB/s from beyond its L2 while it multiplies
+    const double tbps = std::min(6.2e6, is_direct(c.tile) ? 0.036e6 * (double)std::min<int64_t>(n, cu_count) : 6.2e6);
+    us = with_floor(us, 3.0 + operand_bytes(M, N, K, batch) / tbps + output_bytes(M, N, batch) / (c.c_tbps * 1e6));
+    if (split > 1 && combines(c.tile, split))
+        us += c.combine_base + c.combine_each * split;
+    else if (split > 1)
         us += c.split_base + c.split_each * split + (2.0 * split + 1.0) * output_bytes(M, N, 1) * c.us_per_byte;
-    return with_floor(us, 3.0 + operand_bytes(M, N, K, batch) / 6.2e6 + output_bytes(M, N, batch) / (c.c_tbps * 1e6));
+    return us;
 }
 
 // Modelled time of the tile plan `cfg` for these operands: the geometric mean
 // of the two models (the tile model alone is 10-20% low on one round of 128 x
 // 128 tiles, the launch model 10-40% high on short K; between them 2 of the
-// 580 shapes lose by more than 3%).  No call is faster than its bytes at 4.2 TB/s (few rows leave most of each
+// 580 shapes lose by more than 3%).  No call is faster than its bytes at 4.3 TB/s (few rows leave most of each
 // tile's loads to A's last row), plus the copies of operands the pipelined
 // kernels cannot read in place; for K ranges under three steps, the general
 // kernel's rounds.  Fitted to the same shapes as the launches.
@@ -485,15 +518,15 @@ double plan_cost(int64_t M, int64_t N, int64_t K, bool copy_a, bool copy_b, int6
                  int cu_count)
 {
     const TileShape &t = kTiles[cfg.tile];
-    const double floor_us = 3.0 + (operand_bytes(M, N, K, batch) + output_bytes(M, N, batch)) / 4.24e6;
+    const double floor_us = 3.0 + (operand_bytes(M, N, K, batch) + output_bytes(M, N, batch)) / 4.29e6;
     const int64_t steps = cdiv(std::min(split_chunk(K, cfg.split_k, t.bk), K), t.bk);
     if (steps < 3) {
         const int64_t n = cdiv(M, t.bm) * cdiv(N, t.bn) * cfg.split_k * batch;
-        const double us = 10.0 + (double)(cdiv(n, cu_count) * steps * (t.bm * t.bn / 16384)) * 2.16 *
-                                     (copy_a || copy_b ? 1.82 : 1.0);
+        const double us = 10.0 + (double)(cdiv(n, cu_count) * steps * (t.bm * t.bn / 16384)) * 2.12 *
+                                     (copy_a || copy_b ? 1.77 : 1.0);
         return with_floor(us, floor_us);
     }
-    const double tile_us = with_floor(0.899 * model_cost(M * batch, N, K, cu_count, cfg.tile, cfg.split_k) + 3.03, floor_us);
+    const double tile_us = with_floor(0.914 * model_cost(M * batch, N, K, cu_count, cfg.tile, cfg.split_k) + 2.74, floor_us);
     const double launch_us = launch_cost(kPlanCost[cfg.tile], M, N, K, batch, false, false, cfg.split_k, cu_count);
     return sqrt(tile_us * launch_us) + copy_cost(M, N, K, copy_a, copy_b, batch);
 }
@@ -780,7 +813,7 @@ struct Segment {
     bool dma;    // pipelined direct-to-LDS kernel (else the general one)
     bool sk;     // the persistent stream-K kernel (the 256 x 256 tile; dma is set too)
     bool vec_c;  // output 16-byte aligned, ldc a multiple of 4 (the persistent kernel's buffer stores)
-    int reduce;  // 0: writes C; 1: full-matrix partials + splitk_reduce
+    int reduce;  // 0: writes C; 1: full-matrix partials + splitk_reduce; 2: partial blocks, added by the last workgroup
     int dp_rounds, sk_tiles, kt;  // persistent kernel: rounds of whole tiles, shared tiles, K steps per tile
 };
 
@@ -905,6 +938,8 @@ int make_plan_with(int64_t M, int64_t N, int64_t K, const void *A, int64_t lda, 
     base.tile_base = 0;
     base.batch = 1;
     base.stride_a = base.stride_b = base.stride_c = 0;
+    base.part = nullptr;
+    base.count = nullptr;
     out->tile = cfg.tile;
     out->ldw = cdiv(N, 4) * 4;
     out->ws = 0;
@@ -959,6 +994,14 @@ int make_plan_with(int64_t M, int64_t N, int64_t K, const void *A, int64_t lda, 
         return make_plan_with(M, N, K, A, lda, B, ldb, C, ldc, other, cu_count, pk, out);
     }
     if (split > 1) {
+        const size_t block = direct_block_bytes(cfg.tile);
+        if (combines(cfg.tile, split) && tiles <= kMaxSkGrid) {
+            // the last workgroup of each tile adds the partial blocks
+            add(0, tiles, split, kc, 0);
+            out->seg[0].reduce = 2;
+            out->ws = (size_t)tiles * (size_t)split * block;
+            return finish();
+        }
         add(0, tiles, split, kc, 1);
         out->ws = workspace_bytes(M, N, split);
         return finish();
@@ -1304,8 +1347,12 @@ int launch_plan(xgemm_ctx *h, Plan plan, char *ws, int64_t M, int64_t N, int64_t
             g.p.A = (const uint16_t *)(ws + pk.a_off);
         if (pk.b)
             g.p.B = (const uint16_t *)(ws + pk.b_off);
-        if (g.reduce)
+        if (g.reduce == 1)
             g.p.C = (float *)ws;
+        if (g.reduce == 2) {
+            g.p.part = (float *)ws;
+            g.p.count = flags;
+        }
         e = g.sk ? launch_sk(dtype, sk_params(g, flags, (float *)ws), s)
                  : launch_tile(plan.tile, g.dma, dtype, g.p, (int)g.grid, s);
         if (e != hipSuccess) {
@@ -1319,7 +1366,7 @@ int launch_plan(xgemm_ctx *h, Plan plan, char *ws, int64_t M, int64_t N, int64_t
                                (const float *)ws, (int64_t)(M * plan.ldw), plan.ldw, g.p.split, C,
                                ldc, (int)M, (int)N);
         }
-        if (g.reduce) {
+        if (g.reduce == 1) {
             e = hipGetLastError();
             if (e != hipSuccess) {
                 set_error(h, "split-k reduce launch", e);
@@ -1635,6 +1682,9 @@ int run_gemv(xgemm_ctx *h, int64_t M, int64_t K, const float *A, int64_t lda, co
 struct TraceSplit {
     int schedule = 0;
     const int *tail = nullptr, *head = nullptr;
+    // register-direct kernel: a tile's counter and the count this workgroup finds
+    const int *count = nullptr;
+    int found = 0;
     std::vector<int> words;
 };
 
@@ -1754,6 +1804,8 @@ struct TraceOps {
     int flag_add(int *f, int) const
     {
         push(XGEMM_TRACE_LOAD, 4, 0, (int64_t)(uintptr_t)f);
+        if (split && f == split->count)
+            return split->found;
         // the piece counting in second finds 1: the tail under schedule 1
         return (split && f == split->tail && split->schedule == 1) ? 1 : 0;
     }
@@ -2140,8 +2192,12 @@ int xgemm_trace_workgroup(int64_t M, int64_t N, int64_t K, const void *A, int64_
     if (g.reduce || pk.a || pk.b || (g.sk && g.sk_tiles > 0)) {
         if (!W)
             return XGEMM_ERR_INVALID_ARG;
-        if (g.reduce)
+        if (g.reduce == 1)
             g.p.C = (float *)wdata;
+        if (g.reduce == 2) {
+            g.p.part = (float *)wdata;
+            g.p.count = (int *)W;
+        }
         if (pk.a)
             g.p.A = (const uint16_t *)(wdata + pk.a_off);
         if (pk.b)
@@ -2165,6 +2221,13 @@ int xgemm_trace_workgroup(int64_t M, int64_t N, int64_t K, const void *A, int64_
         }
         return (int)XGEMM_OK;
     };
+    if (is_direct(plan.tile) && g.reduce == 2) {
+        // under schedule 0 a tile's last K range counts in last, under 1 its first
+        int tm, tn, ks, local;
+        (void)xgemm_dev::map_tile(g.p, (int)block, (int)g.grid, tm, tn, ks, local);
+        split.count = g.p.count + local;
+        split.found = ks == (schedule == 0 ? g.p.split - 1 : 0) ? g.p.split - 1 : 0;
+    }
     if (is_direct(plan.tile))
         return with_direct_tile(plan.tile, [&](auto t) {
             using T = decltype(t);

@@ -428,11 +428,15 @@ class _Coverage:
         self.sk = info.family == xg.XGEMM_KERNEL_PERSISTENT
         self.M, self.N, self.ldc, self.bm, self.bn = M, N, ldc, bm, bn
         self.split = info.split
-        self.count = np.zeros((M, N), dtype=np.uint8) if info.reduce == 0 else None
+        self.count = np.zeros((M, N), dtype=np.uint8) if info.reduce != 1 else None
         self.ldw = (N + 3) // 4 * 4
         if info.reduce == 1:
             self.pbase = BASE_W + info.data_offset
             self.part = np.zeros((info.split, M, N), dtype=np.uint8)
+        elif info.reduce == 2:
+            # one block of bm x bn floats per tile and K range
+            self.pbase = BASE_W + info.data_offset
+            self.part = np.zeros(info.tile_count * info.split * bm * bn, dtype=np.uint8)
         elif self.sk:
             self.pbase = BASE_W + info.data_offset
             self.part = np.zeros(2 * info.grid * bm * bn, dtype=np.uint8)
@@ -459,6 +463,13 @@ class _Coverage:
     def add(self, addr, nbytes):
         """Record stores of nbytes at each address; returns a list of problems."""
         bad = []
+        if nbytes == 4 and self.reduce == 2:
+            # counter resets, and C element by element
+            ctr = addr >= BASE_W
+            off = addr[ctr] - BASE_W
+            if ((off >= PREFIX_BYTES) | (off % 4 != 0)).any():
+                bad.append("4-byte store outside the counter prefix")
+            addr = addr[~ctr]
         if self.sk and nbytes == 4:
             # counter resets
             off = addr - BASE_W
@@ -494,7 +505,7 @@ class _Coverage:
         return ok
 
     def result(self):
-        arr = self.count if self.reduce == 0 else self.part
+        arr = self.part if self.reduce == 1 else self.count
         zero = int((arr == 0).sum())
         many = int((arr > 1).sum())
         return zero, many
@@ -538,7 +549,8 @@ def check_launch(M, N, K, cfg, cu_count=256, lda=None, ldb=None, ldc=None, max_b
     for seg in range(info0.segments):
         info = xg.xgemm_trace_plan(M, N, K, BASE_A, lda, BASE_B, ldb, BASE_C, ldc, cfg, cu_count, seg)
         sk = info.family == xg.XGEMM_KERNEL_PERSISTENT
-        scheds = schedules if schedules is not None else ((0, 1) if sk and info.sk_tiles > 0 else (0,))
+        shared = (sk and info.sk_tiles > 0) or info.reduce == 2   # partial sums read back in the same launch
+        scheds = schedules if schedules is not None else ((0, 1) if shared else (0,))
         nblk = info.grid if max_blocks is None else min(info.grid, max_blocks)
         for schedule in scheds:
             cov = _Coverage(info, M, N, ldc, bm, bn)
@@ -555,7 +567,7 @@ def check_launch(M, N, K, cfg, cu_count=256, lda=None, ldb=None, ldc=None, max_b
                 ga = ev["addr"][ld]
                 nb = ev["arg"][ld]
                 inside = ((ga >= a_lo) & (ga + nb <= a_hi)) | ((ga >= b_lo) & (ga + nb <= b_hi))
-                if sk:
+                if sk or info.reduce == 2:
                     ctr = (ga >= BASE_W) & (ga + nb <= BASE_W + PREFIX_BYTES) & (nb == 4)
                     part = (ga >= BASE_W + info.data_offset) & (ga + nb <= BASE_W + info.workspace_bytes) & (nb == 16)
                     inside |= ctr | part
@@ -588,16 +600,16 @@ def check_launch(M, N, K, cfg, cu_count=256, lda=None, ldb=None, ldc=None, max_b
             if max_blocks is not None:
                 continue
             zero, many = cov.result()
-            tag = "launch %d%s" % (seg, " (schedule %d)" % schedule if sk else "")
+            tag = "launch %d%s" % (seg, " (schedule %d)" % schedule if shared else "")
             if many:
                 violations.append(Violation("coverage", -1, -1, "%s: %d output elements stored by more than one "
                                             "store (unordered workgroups race)" % (tag, many)))
             if zero and info.reduce == 1:
                 violations.append(Violation("coverage", -1, -1, "%s: %d partial elements never written" %
                                             (tag, zero)))
-            if info.reduce == 0 and zero:
+            if info.reduce != 1 and zero:
                 violations.append(Violation("coverage", -1, -1, "%s: %d elements of C never written" % (tag, zero)))
-            if sk:
+            if sk or info.reduce == 2:
                 if cov.partial_many():
                     violations.append(Violation("coverage", -1, -1, "%s: %d partial-sum elements stored twice" %
                                                 (tag, cov.partial_many())))

@@ -146,3 +146,87 @@ def test_infinities_stay_in_their_rows():
     for tile in DIRECT:
         C = xg.gemm(A, B, config=_cfg(tile))
         assert torch.all(torch.isinf(C[M - 1])) and torch.all(C[:M - 1] == K), tile
+
+
+# (M, N, K, split) with partial blocks added by the last workgroup of a tile:
+# two ranges and the most, one tile and several, ragged rows and columns
+COMBINED = [(1, 8, 512, 2), (16, 300, 1101, 4), (70, 136, 2000, 3), (65, 257, 4160, 4)]
+
+
+@pytest.mark.parametrize("tile", [t for t in DIRECT if t <= xg.XGEMM_DIRECT_32x256])
+@pytest.mark.parametrize("case", COMBINED, ids=lambda c: "x".join(map(str, c)))
+def test_combined_split_traces(tile, case):
+    M, N, K, split = case
+    info = xg.xgemm_trace_plan(M, N, K, sc.BASE_A, K, sc.BASE_B, N, sc.BASE_C, N, _cfg(tile, split), 256, 0)
+    assert info.reduce == 2
+    rep = sc.check_launch(M, N, K, _cfg(tile, split))
+    assert rep.ok, [str(v) for v in rep.violations]
+
+
+def test_combined_split_planted_mistake():
+    """A workgroup that reads the others' blocks without having found itself
+    last, or a block that nobody stored, is caught as partials read back that
+    no workgroup stores."""
+    tile, (M, N, K, split) = xg.XGEMM_DIRECT_32x64, (40, 70, 900, 3)
+    real = sc.trace_workgroup
+
+    def without_first_range(m, n, k, lda, ldb, ldc, cfg, cu, seg, block, threads, capacity=None, schedule=0):
+        ev, counts = real(m, n, k, lda, ldb, ldc, cfg, cu, seg, block, threads, capacity, schedule)
+        part = (ev["op"] == sc.STORE) & (ev["addr"] >= sc.BASE_W + sc.PREFIX_BYTES) & (ev["arg"] == 16)
+        if block == 0:
+            ev["addr"][part] += 1 << 20
+        return ev, counts
+    mp = pytest.MonkeyPatch()
+    try:
+        mp.setattr(sc, "trace_workgroup", without_first_range)
+        rep = sc.check_launch(M, N, K, _cfg(tile, split))
+    finally:
+        mp.undo()
+    assert not rep.ok
+
+
+def test_deep_splits_take_a_second_launch():
+    """More partial blocks than one CU should read, or waves that share no
+    block: the separate reduction."""
+    for tile, split in [(xg.XGEMM_DIRECT_64x128, 5), (xg.XGEMM_DIRECT_64x64, 9), (xg.XGEMM_DIRECT_64x256, 2)]:
+        info = xg.xgemm_trace_plan(64, 256, 16384, sc.BASE_A, 16384, sc.BASE_B, 256, sc.BASE_C, 256, _cfg(tile, split),
+                                   256, 0)
+        assert info.reduce == 1, tile
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("tile", [t for t in DIRECT if t <= xg.XGEMM_DIRECT_32x256])
+@pytest.mark.parametrize("case", COMBINED, ids=lambda c: "x".join(map(str, c)))
+def test_combined_split(tile, case):
+    """Against the oracle; the same bits on every run (whichever workgroup is
+    last, and with the counters left at zero) and on graph replays with eager
+    calls between them."""
+    import torch
+    from gpu_util import check_close, to_device
+    M, N, K, split = case
+    oracle.build(force=False)
+    A, B = wl.make_inputs(M, N, K, "bf16", "uniform", M + K)
+    C_ref, S = oracle.gemm(A, B, "bf16")
+    dA, dB, st = to_device(A, "bf16"), to_device(B, "bf16"), torch.cuda.Stream()
+    cfg, out = _cfg(tile, split), torch.empty(M, N, device="cuda")
+    torch.cuda.synchronize()
+    xg.gemm(dA, dB, out=out, config=cfg, stream=st)
+    st.synchronize()
+    first = out.clone()
+    check_close(first.cpu().numpy(), C_ref, S, "combined %d %s" % (tile, case))
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=st):
+        for _ in range(3):
+            xg.gemm(dA, dB, out=out, config=cfg, stream=st)
+    for _ in range(3):
+        out.fill_(float("nan"))
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, first)
+        out.fill_(float("nan"))
+        torch.cuda.synchronize()
+        xg.gemm(dA, dB, out=out, config=cfg, stream=st)
+        torch.cuda.synchronize()
+        assert torch.equal(out, first)
