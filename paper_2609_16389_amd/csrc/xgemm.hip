@@ -1608,7 +1608,6 @@ GemvParams gemv_params(int64_t M, int64_t K, const float *A, int64_t lda, const 
     int64_t kc;
     p.split = gemv_split(K, split_k, &kc);
     p.k_chunk = (int)kc;
-    p.vec = ((uintptr_t)A % 16 == 0) && ((uintptr_t)x % 16 == 0) && (lda % 4 == 0);
     const int64_t blocks = cdiv(M, rows) * p.split;
     p.blocks = blocks <= 0x7fffffff ? (int)blocks : 0;
     return p;
