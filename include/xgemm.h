@@ -149,11 +149,11 @@ int xgemm_set_persistent(xgemm_handle_t h, int enable);
  * A pointer may be NULL only when its matrix has no elements.  Aligned fast
  * path: A, B 16-byte aligned, lda, ldb, K and N multiples of 8 (C: any
  * alignment and ldc).  Any other layout is
- * still correct: the operands that miss these conditions are first copied,
- * zero-padded, into the handle's workspace (M x K rounded up to 8 for A, K x N
- * both rounded up to 8 for B; both when K is not a multiple of 8), or, where
- * K is too short for the pipelined kernels (under about 3 steps of 64 per
- * split), read in place by a slower element-wise kernel.  Sizes are limited
+ * still correct: the register-direct kernel reads it in place where that is
+ * faster (few output tiles, short K), else the operands that miss these
+ * conditions are first copied, zero-padded, into the handle's workspace
+ * (M x K rounded up to 8 for A, K x N both rounded up to 8 for B; both when K
+ * is not a multiple of 8).  Sizes are limited
  * to M, N, K < 2^31 with every matrix addressable in 64-bit element offsets.  A handle holds one workspace
  * (split-k partials and operand copies), grown on demand with hipMalloc
  * (XGEMM_ERR_ALLOC if that fails).  Calls that share a handle may be
@@ -510,9 +510,10 @@ typedef struct xgemv_config {
  *   A, lda   device pointer to M x K floats, lda >= K
  *   x        device pointer to K floats
  *   y        device pointer to M floats; must not overlap A or x
- * A pointer may be NULL only when it addresses no element.  16-byte loads
- * need A and x 16-byte aligned and lda a multiple of 4; any other alignment
- * is still correct through 4-byte loads.  The handle supplies the device's
+ * A pointer may be NULL only when it addresses no element.  A and x on
+ * 16-byte boundaries with lda a multiple of 4 are read 16 bytes at a time, and
+ * so is any other layout where the launch is small; the result does not depend
+ * on it.  The handle supplies the device's
  * CU count, and its workspace holds the partial sums of a K split
  * (split_k * M floats; ordered across streams as for xgemm_run).  Errors:
  * XGEMM_ERR_INVALID_ARG for a NULL handle, bad sizes or pointers, or a

@@ -27,7 +27,7 @@
 // last row, shifted and zeroed.  That needs N and K of at least 8.
 //
 // What bounds it: with few rows, the bytes of B (16 x 14336 x 4096, 117 MB:
-// 25.4 us, 4.6 TB/s, against 30.1 for 128 x 128 tiles through LDS, whose A
+// 24.8 us, 4.7 TB/s, against 30.1 for 128 x 128 tiles through LDS, whose A
 // tile is 7/8 padding and whose pipeline keeps 32 KiB in flight per CU; here
 // 8 waves hold 9 KiB each).  With few tiles, latency: 256^3 3.7 us against
 // 6.0, 1000^3 9.5 against 20.9 (256 workgroups against 64).  With many tiles

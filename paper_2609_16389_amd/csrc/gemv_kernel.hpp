@@ -38,6 +38,7 @@ struct GemvParams {
     int M, K;
     int k_chunk;  // K values per split, a multiple of 4 (K when split == 1)
     int split;
+    int vec;      // 16-byte loads, several chunks ahead (else 4-byte loads, one chunk at a time)
     int blocks;   // workgroups of the launch, ceil(M / R) * split; a 2-D grid may hold more, which exit
 };
 
@@ -117,27 +118,46 @@ __host__ __device__ __forceinline__ void gemv_block(const Ops &ops, const GemvPa
 
     const int K4 = kn / 4;  // whole chunks of 4 values
     int c = tid;
-    for (; c + (U - 1) * kThreads < K4; c += U * kThreads) {
-        f32x4 xv[U], av[R][U];
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-            xv[u] = ops.load4(xq + 4 * (c + u * kThreads));
-#pragma unroll
-        for (int r = 0; r < R; ++r)
+    if (p.vec) {
+        for (; c + (U - 1) * kThreads < K4; c += U * kThreads) {
+            f32x4 xv[U], av[R][U];
 #pragma unroll
             for (int u = 0; u < U; ++u)
-                av[r][u] = ops.load4(arow[r] + 4 * (c + u * kThreads));
-#pragma unroll
-        for (int u = 0; u < U; ++u)
+                xv[u] = ops.load4(xq + 4 * (c + u * kThreads));
 #pragma unroll
             for (int r = 0; r < R; ++r)
-                acc[r] = fma4(av[r][u], xv[u], acc[r]);
-    }
-    for (; c < K4; c += kThreads) {
-        const f32x4 xv = ops.load4(xq + 4 * c);
 #pragma unroll
-        for (int r = 0; r < R; ++r)
-            acc[r] = fma4(ops.load4(arow[r] + 4 * c), xv, acc[r]);
+                for (int u = 0; u < U; ++u)
+                    av[r][u] = ops.load4(arow[r] + 4 * (c + u * kThreads));
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int r = 0; r < R; ++r)
+                    acc[r] = fma4(av[r][u], xv[u], acc[r]);
+        }
+        for (; c < K4; c += kThreads) {
+            const f32x4 xv = ops.load4(xq + 4 * c);
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+                acc[r] = fma4(ops.load4(arow[r] + 4 * c), xv, acc[r]);
+        }
+    } else {
+        for (; c < K4; c += kThreads) {
+            f32x4 xv;
+            xv.x = ops.load1(xq + 4 * c);
+            xv.y = ops.load1(xq + 4 * c + 1);
+            xv.z = ops.load1(xq + 4 * c + 2);
+            xv.w = ops.load1(xq + 4 * c + 3);
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                f32x4 av;
+                av.x = ops.load1(arow[r] + 4 * c);
+                av.y = ops.load1(arow[r] + 4 * c + 1);
+                av.z = ops.load1(arow[r] + 4 * c + 2);
+                av.w = ops.load1(arow[r] + 4 * c + 3);
+                acc[r] = fma4(av, xv, acc[r]);
+            }
+        }
     }
     // the range's last kn % 4 values, one per thread
     const int kt = 4 * K4 + tid;

@@ -1594,8 +1594,16 @@ int check_gemv_args(int64_t M, int64_t K, const float *A, int64_t lda, const flo
 // Launch parameters of a GEMV with `rows` rows per workgroup; blocks is 0
 // when the launch would exceed 2^31 - 1 workgroups (only possible with a
 // forced split of a very tall matrix), which callers reject.
+//
+// 16-byte loads where rows of A and x start on 16-byte boundaries, and, since
+// the memory path needs dword alignment only, on any layout that gives fewer
+// than two workgroups per CU: there the loads in flight count (64 x 65535
+// 9.2 against 20.5 us with 4-byte loads, 300 x 30003 9.0 against 11.8).  With
+// more, the 16-byte loads that straddle lines cost what they gain (1023 x
+// 20003 14.3 against 13.9 us, 1304 x 12607 11.9 against 11.5).  The sums and
+// their order are the same.
 GemvParams gemv_params(int64_t M, int64_t K, const float *A, int64_t lda, const float *x, float *y, int rows,
-                       int split_k, float *part)
+                       int split_k, float *part, int cu_count)
 {
     GemvParams p;
     p.A = A;
@@ -1609,6 +1617,7 @@ GemvParams gemv_params(int64_t M, int64_t K, const float *A, int64_t lda, const 
     p.split = gemv_split(K, split_k, &kc);
     p.k_chunk = (int)kc;
     const int64_t blocks = cdiv(M, rows) * p.split;
+    p.vec = (((uintptr_t)A % 16 == 0) && ((uintptr_t)x % 16 == 0) && (lda % 4 == 0)) || blocks < 2 * (int64_t)cu_count;
     p.blocks = blocks <= 0x7fffffff ? (int)blocks : 0;
     return p;
 }
@@ -1636,7 +1645,7 @@ int run_gemv(xgemm_ctx *h, int64_t M, int64_t K, const float *A, int64_t lda, co
             cfg = *forced;
         else
             select_gemv(M, K, h->cu_count, &cfg);
-        GemvParams p = gemv_params(M, K, A, lda, x, y, cfg.rows, cfg.split_k, nullptr);
+        GemvParams p = gemv_params(M, K, A, lda, x, y, cfg.rows, cfg.split_k, nullptr, h->cu_count);
         if (p.blocks == 0)
             return XGEMM_ERR_INVALID_ARG;
         if (p.split > 1) {
@@ -2291,7 +2300,7 @@ int xgemv_trace_workgroup(int64_t M, int64_t K, const float *A, int64_t lda, con
     if (!counts || capacity < 0 || (capacity > 0 && !out) || !valid_gemv_config(cfg) || M <= 0 || K <= 0 ||
         check_gemv_args(M, K, A, lda, x, y) != XGEMM_OK)
         return XGEMM_ERR_INVALID_ARG;
-    const GemvParams p = gemv_params(M, K, A, lda, x, y, cfg->rows, cfg->split_k, W);
+    const GemvParams p = gemv_params(M, K, A, lda, x, y, cfg->rows, cfg->split_k, W, 256);
     if (p.blocks == 0 || block < 0 || block >= p.blocks || (p.split > 1 && !W))
         return XGEMM_ERR_INVALID_ARG;
     return with_gemv_config(*cfg, [&](auto r, auto u) {
