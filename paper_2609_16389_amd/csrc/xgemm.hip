@@ -383,8 +383,10 @@ BandPlan select_band(int64_t M, int64_t N, int64_t K, int cu_count, bool persist
 // Selections a handle has made, by what they depend on: sizes and layout
 // flags (no address).  Evaluating the models takes 0.5 to 6 us of host time
 // per call, as long as a small product runs; programs repeat few shapes.
-// Direct-mapped and of fixed size; a handle is used by one host thread at a
-// time, so nothing is locked.
+// Direct-mapped and of fixed size.  Callers from Python share a handle
+// between threads, and the binding drops the interpreter's lock for the call:
+// an entry is copied in and out whole under `lock` (some 20 ns uncontended),
+// and evaluated outside it.
 struct PlanCache {
     static constexpr int kSlots = 128;
     struct Band {
@@ -397,6 +399,7 @@ struct PlanCache {
         int flags = 0;
         xgemm_config from{}, to{};
     } launch[kSlots];
+    std::mutex lock;
     static int slot(int64_t M, int64_t N, int64_t K)
     {
         const uint64_t x = ((uint64_t)M * 0x9E3779B97F4A7C15ull) ^ ((uint64_t)N * 0xC2B2AE3D27D4EB4Full) ^
@@ -411,12 +414,16 @@ BandPlan cached_band(PlanCache *cache, int64_t M, int64_t N, int64_t K, int cu_c
 {
     if (!cache)
         return select_band(M, N, K, cu_count, persistent);
-    PlanCache::Band &e = cache->band[PlanCache::slot(M, N, K)];
-    if (e.M != M || e.N != N || e.K != K || e.persistent != (int)persistent) {
-        e.plan = select_band(M, N, K, cu_count, persistent);
-        e.M = M, e.N = N, e.K = K, e.persistent = (int)persistent;
+    PlanCache::Band &slot = cache->band[PlanCache::slot(M, N, K)];
+    {
+        std::lock_guard<std::mutex> hold(cache->lock);
+        if (slot.M == M && slot.N == N && slot.K == K && slot.persistent == (int)persistent)
+            return slot.plan;
     }
-    return e.plan;
+    const PlanCache::Band made{M, N, K, (int)persistent, select_band(M, N, K, cu_count, persistent)};
+    std::lock_guard<std::mutex> hold(cache->lock);
+    slot = made;
+    return made.plan;
 }
 
 // The launches xgemm_run considers beside the selected tile plan: a 128 x 128
@@ -547,11 +554,14 @@ void select_launch(int64_t M, int64_t N, int64_t K, const void *A, int64_t lda, 
     const bool odd_a = (uintptr_t)A % 4 != 0 || lda % 2 != 0 || sa % 2 != 0;
     const bool odd_b = (uintptr_t)B % 4 != 0 || ldb % 2 != 0 || sb % 2 != 0;
     const int flags = copy_a | copy_b << 1 | odd_a << 2 | odd_b << 3 | may_split << 4;
-    PlanCache::Launch *const e = cache ? &cache->launch[PlanCache::slot(M, N, K)] : nullptr;
-    if (e && e->M == M && e->N == N && e->K == K && e->batch == batch && e->flags == flags &&
-        e->from.tile == cfg->tile && e->from.split_k == cfg->split_k && e->from.group_m == cfg->group_m) {
-        *cfg = e->to;
-        return;
+    PlanCache::Launch *const slot = cache ? &cache->launch[PlanCache::slot(M, N, K)] : nullptr;
+    if (slot) {
+        std::lock_guard<std::mutex> hold(cache->lock);
+        if (slot->M == M && slot->N == N && slot->K == K && slot->batch == batch && slot->flags == flags &&
+            slot->from.tile == cfg->tile && slot->from.split_k == cfg->split_k && slot->from.group_m == cfg->group_m) {
+            *cfg = slot->to;
+            return;
+        }
     }
     const xgemm_config from = *cfg;
     double best = kLaunchMargin * plan_cost(M, N, K, copy_a, copy_b, batch, *cfg, cu_count);
@@ -581,11 +591,10 @@ void select_launch(int64_t M, int64_t N, int64_t K, const void *A, int64_t lda, 
             }
         }
     }
-    if (e) {
-        e->M = M, e->N = N, e->K = K, e->batch = batch;
-        e->flags = flags;
-        e->from = from;
-        e->to = *cfg;
+    if (slot) {
+        const PlanCache::Launch made{M, N, K, batch, flags, from, *cfg};
+        std::lock_guard<std::mutex> hold(cache->lock);
+        *slot = made;
     }
 }
 

@@ -387,7 +387,10 @@ def handle(device_index: int | None = None, stream=None):
     A handle's workspace (split-k partials, operand copies) belongs to one
     stream at a time: the library orders calls that share it across streams
     after each other, so one handle per stream is what lets calls on
-    different streams run concurrently.  ``stream`` is a torch stream, a raw
+    different streams run concurrently.  Threads on one stream share its
+    handle: their calls need no order of their own as long as they need no
+    workspace; where they do, the program makes the calls one at a time or
+    gives each thread a stream.  ``stream`` is a torch stream, a raw
     hipStream_t address or None (the null stream)."""
     import torch
     if device_index is None:

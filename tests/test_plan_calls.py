@@ -1,0 +1,33 @@
+"""What calls are planned as, where only a handle's state shows it: the table
+of selections under several threads.  The library's host code is compiled
+alone and run on the CPU."""
+import os
+import subprocess
+
+import pytest
+
+from paper_2609_16389_amd import build
+
+_SRC = os.path.join(os.path.dirname(os.path.abspath(__file__)), "host", "plan_calls.cpp")
+
+
+@pytest.fixture(scope="module")
+def host(tmp_path_factory):
+    exe = str(tmp_path_factory.mktemp("host") / "plan_calls")
+    # (the symbol of the GPU code stays unresolved: nothing here launches)
+    subprocess.run([build.HIPCC, "-x", "hip", "--offload-host-only", "-std=c++20", "-O1", "-pthread",
+                    "-I" + os.path.join(build.ROOT, "include"), _SRC, "-Wl,--unresolved-symbols=ignore-all", "-o", exe],
+                   check=True)
+
+    def run(*args):
+        r = subprocess.run([exe] + [str(a) for a in args], capture_output=True, text=True, timeout=120)
+        assert r.returncode == 0, "%s: status %d\n%s%s" % (args, r.returncode, r.stdout, r.stderr)
+        return r.stdout
+    return run
+
+
+@pytest.mark.parametrize("count", [1, 2, 4])
+def test_threads_share_a_table(host, count):
+    """Python threads share one handle per stream, and the interpreter's lock
+    is not held during a call."""
+    host("threads", count)
