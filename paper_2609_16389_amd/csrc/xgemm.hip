@@ -400,12 +400,16 @@ struct PlanCache {
         xgemm_config from{}, to{};
     } launch[kSlots];
     std::mutex lock;
-    static int slot(int64_t M, int64_t N, int64_t K)
+    static int slot(int64_t M, int64_t N, int64_t K, int64_t batch = 1, int flags = 0)
     {
         const uint64_t x = ((uint64_t)M * 0x9E3779B97F4A7C15ull) ^ ((uint64_t)N * 0xC2B2AE3D27D4EB4Full) ^
-                           ((uint64_t)K * 0x165667B19E3779F9ull);
+                           ((uint64_t)K * 0x165667B19E3779F9ull) ^
+                           ((uint64_t)(batch * 32 + flags) * 0x27D4EB2F165667C5ull);
         return (int)(x >> 57);
     }
+    // the plans with and without the persistent kernel of one shape never
+    // share a slot: a call whose operands that kernel cannot take looks up both
+    static int band_slot(int64_t M, int64_t N, int64_t K, bool persistent) { return slot(M, N, K) ^ (int)persistent; }
 };
 
 namespace {
@@ -414,7 +418,7 @@ BandPlan cached_band(PlanCache *cache, int64_t M, int64_t N, int64_t K, int cu_c
 {
     if (!cache)
         return select_band(M, N, K, cu_count, persistent);
-    PlanCache::Band &slot = cache->band[PlanCache::slot(M, N, K)];
+    PlanCache::Band &slot = cache->band[PlanCache::band_slot(M, N, K, persistent)];
     {
         std::lock_guard<std::mutex> hold(cache->lock);
         if (slot.M == M && slot.N == N && slot.K == K && slot.persistent == (int)persistent)
@@ -554,7 +558,7 @@ void select_launch(int64_t M, int64_t N, int64_t K, const void *A, int64_t lda, 
     const bool odd_a = (uintptr_t)A % 4 != 0 || lda % 2 != 0 || sa % 2 != 0;
     const bool odd_b = (uintptr_t)B % 4 != 0 || ldb % 2 != 0 || sb % 2 != 0;
     const int flags = copy_a | copy_b << 1 | odd_a << 2 | odd_b << 3 | may_split << 4;
-    PlanCache::Launch *const slot = cache ? &cache->launch[PlanCache::slot(M, N, K)] : nullptr;
+    PlanCache::Launch *const slot = cache ? &cache->launch[PlanCache::slot(M, N, K, batch, flags)] : nullptr;
     if (slot) {
         std::lock_guard<std::mutex> hold(cache->lock);
         if (slot->M == M && slot->N == N && slot->K == K && slot->batch == batch && slot->flags == flags &&

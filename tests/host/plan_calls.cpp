@@ -84,6 +84,21 @@ int threads(int count)
     return sum != 0;
 }
 
+// A persistent plan whose operands that kernel cannot take: the plans with and
+// without it stay in the table together.
+int kept()
+{
+    const Shape s{8192, 8192, 8192, 8192 + 1, 8192};
+    PlanCache table;
+    CallPlan cp;
+    plan(s, true, 0, &table, &cp);
+    int found = 0;
+    for (const PlanCache::Band &e : table.band)
+        if (e.M == s.M && e.N == s.N && e.K == s.K)
+            found |= 1 << e.persistent;
+    return found != 3;
+}
+
 }  // namespace
 
 int main(int argc, char **argv)
@@ -91,5 +106,7 @@ int main(int argc, char **argv)
     const char *what = argc > 1 ? argv[1] : "";
     if (!strcmp(what, "threads"))
         return threads(atoi(argv[2]));
+    if (!strcmp(what, "kept"))
+        return kept();
     return 2;
 }

@@ -31,3 +31,8 @@ def test_threads_share_a_table(host, count):
     """Python threads share one handle per stream, and the interpreter's lock
     is not held during a call."""
     host("threads", count)
+
+
+def test_both_plans_of_a_shape_are_kept(host):
+    """With and without the persistent kernel: neither lookup evicts the other."""
+    host("kept")
