@@ -119,8 +119,11 @@ int xgemm_destroy(xgemm_handle_t h);
  * Cap the device memory the handle's workspace may hold at `bytes` (0, the
  * default: no cap).  A later call that needs a larger workspace returns
  * XGEMM_ERR_ALLOC and enqueues nothing, as when hipMalloc fails; a
- * workspace already larger than the cap is kept.  For callers that budget
- * device memory.  XGEMM_ERR_INVALID_ARG for a NULL handle.
+ * workspace already larger than the cap is kept.  A call that fits the cap
+ * runs as it would without one; where its launch (xgemm_launch_config) does
+ * not fit and the tile plan that launch replaces does, the tile plan runs.
+ * For callers that budget device memory.  XGEMM_ERR_INVALID_ARG for a NULL
+ * handle.
  */
 int xgemm_set_workspace_limit(xgemm_handle_t h, size_t bytes);
 
@@ -165,9 +168,10 @@ int xgemm_set_persistent(xgemm_handle_t h, int enable);
  * one on another stream makes its stream wait for it.  A buffer being grown
  * is freed only after its last user has completed.  Calls on different
  * streams run concurrently only with one handle per stream.  A handle must not be used by two host threads at
- * once.  The configuration comes from the problem shape and the
- * device's CU count (xgemm_select_band: one plan, or a body and a band of C
- * launched one after the other).
+ * once.  The configuration comes from the problem shape, the operands' layout
+ * and the device's CU count (xgemm_select_band: one plan, or a body and a band
+ * of C launched one after the other; xgemm_launch_config: the launch in place
+ * of a single plan's).
  */
 int xgemm_run(xgemm_handle_t h, int64_t M, int64_t N, int64_t K,
               const void *A, int64_t lda, const void *B, int64_t ldb,
@@ -193,7 +197,8 @@ int xgemm_run(xgemm_handle_t h, int64_t M, int64_t N, int64_t K,
  * and must be ordered by the caller.  Returns XGEMM_ERR_INVALID_ARG, with
  * nothing enqueued and the reason in xgemm_last_error, when the call needs
  * more than XGEMM_NOALLOC_SCRATCH_BYTES of scratch (a split-k plan or
- * operand copies too large for it); other errors as xgemm_run.
+ * operand copies too large for it, in the launch that xgemm_run makes); other
+ * errors as xgemm_run.
  */
 #define XGEMM_NOALLOC_SCRATCH_BYTES ((size_t)64 << 20)
 int xgemm_run_noalloc(xgemm_handle_t h, int64_t M, int64_t N, int64_t K,
@@ -234,8 +239,10 @@ int xgemm_run_strided_batched(xgemm_handle_t h, int64_t batch, int64_t M, int64_
                               float *C, int64_t ldc, int64_t stride_c, int dtype, void *stream);
 
 /*
- * The configuration xgemm_run would use for this problem on a device with
- * `cu_count` compute units (host-only; touches no GPU).  Returns
+ * The tile plan's configuration for this problem on a device with `cu_count`
+ * compute units: what xgemm_run uses unless it cuts C in two
+ * (xgemm_select_band) or takes another launch in its place
+ * (xgemm_launch_config).  Host-only; touches no GPU.  Returns
  * XGEMM_ERR_INVALID_ARG for negative sizes, an unknown dtype, cu_count < 1 or
  * out == NULL.
  */
@@ -269,8 +276,9 @@ typedef struct xgemm_band {
 } xgemm_band;
 
 /*
- * The plan xgemm_run would use for this problem on a device with cu_count
- * compute units (host-only; touches no GPU).  A persistent plan
+ * The tile plan of xgemm_run for this problem on a device with cu_count
+ * compute units (host-only; touches no GPU); where it is one ordinary launch,
+ * xgemm_run may take another in its place (xgemm_launch_config).  A persistent plan
  * (body.stream_k = 1) becomes the plan without the persistent kernel when
  * the operands' alignment or leading dimensions do not suit that kernel.  XGEMM_ERR_INVALID_ARG for
  * negative sizes, an unknown dtype, cu_count < 1 or out == NULL.

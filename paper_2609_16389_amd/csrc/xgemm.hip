@@ -397,6 +397,7 @@ struct PlanCache {
     struct Launch {
         int64_t M = -1, N = 0, K = 0, batch = 0;
         int flags = 0;
+        size_t max_ws = 0;
         xgemm_config from{}, to{};
     } launch[kSlots];
     std::mutex lock;
@@ -542,14 +543,56 @@ double plan_cost(int64_t M, int64_t N, int64_t K, bool copy_a, bool copy_b, int6
     return sqrt(tile_us * launch_us) + copy_cost(M, N, K, copy_a, copy_b, batch);
 }
 
+// Bytes of a K split's partial sums: whole blocks that the last workgroup of
+// each tile adds, or full matrices for the separate reduction.
+bool combines_all(int tile, int split, int64_t M, int64_t N)
+{
+    const TileShape t = tile_shape(tile);
+    return combines(tile, split) && cdiv(M, t.bm) * cdiv(N, t.bn) <= kMaxSkGrid;
+}
+size_t split_bytes(int tile, int split, int64_t M, int64_t N)
+{
+    if (split <= 1)
+        return 0;
+    if (combines_all(tile, split, M, N)) {
+        const TileShape t = tile_shape(tile);
+        return (size_t)(cdiv(M, t.bm) * cdiv(N, t.bn)) * (size_t)split * direct_block_bytes(tile);
+    }
+    const int64_t ldw = cdiv(N, 4) * 4;
+    return (size_t)split * (size_t)M * (size_t)ldw * sizeof(float);
+}
+
+// Operands copied into the workspace (pack16) so that the pipelined kernels
+// can run: A as M x k8 (leading dimension k8), B as k8 x n8 (leading
+// dimension n8), with k8 and n8 the K and N rounded up to multiples of 8 and
+// zero padding.  Offsets are bytes from the workspace base.
+struct Pack {
+    bool a = false, b = false;
+    int64_t k8 = 0, n8 = 0;
+    size_t a_off = 0, b_off = 0;
+};
+
+// Place the copies after `ws` bytes of partial sums; the bytes in all.
+size_t place_copies(size_t ws, int64_t M, Pack *pk)
+{
+    if (!pk->a && !pk->b)
+        return ws;
+    pk->a_off = (ws + 255) / 256 * 256;
+    const size_t a_bytes = pk->a ? (size_t)M * (size_t)pk->k8 * 2 : 0;
+    pk->b_off = (pk->a_off + a_bytes + 255) / 256 * 256;
+    return pk->b ? pk->b_off + (size_t)pk->k8 * (size_t)pk->n8 * 2 : pk->a_off + a_bytes;
+}
+
 // Replace *cfg, the tile plan's configuration for `batch` problems, by a
 // launch of the list above where the model puts one ahead.  A candidate adds
 // up an element from at least as many partial sums as the plan it replaces
 // (so its rounding error is no larger).  may_split: the plan uses the
 // workspace, so a K split may too; a call that needed none gets none (it may
-// be one of several on different streams, or under capture).
+// be one of several on different streams, or under capture).  max_ws: the
+// most bytes of workspace a candidate for a single problem may need.
 void select_launch(int64_t M, int64_t N, int64_t K, const void *A, int64_t lda, int64_t sa, const void *B, int64_t ldb,
-                   int64_t sb, int64_t batch, bool may_split, int cu_count, PlanCache *cache, xgemm_config *cfg)
+                   int64_t sb, int64_t batch, bool may_split, size_t max_ws, int cu_count, PlanCache *cache,
+                   xgemm_config *cfg)
 {
     const int plan_chains = cfg->split_k * (cfg->tile == XGEMM_TILE_256x128 ? 2 : 1);
     const bool k_ok = K % 8 == 0;
@@ -562,7 +605,8 @@ void select_launch(int64_t M, int64_t N, int64_t K, const void *A, int64_t lda, 
     if (slot) {
         std::lock_guard<std::mutex> hold(cache->lock);
         if (slot->M == M && slot->N == N && slot->K == K && slot->batch == batch && slot->flags == flags &&
-            slot->from.tile == cfg->tile && slot->from.split_k == cfg->split_k && slot->from.group_m == cfg->group_m) {
+            slot->max_ws == max_ws && slot->from.tile == cfg->tile && slot->from.split_k == cfg->split_k &&
+            slot->from.group_m == cfg->group_m) {
             *cfg = slot->to;
             return;
         }
@@ -584,6 +628,13 @@ void select_launch(int64_t M, int64_t N, int64_t K, const void *A, int64_t lda, 
                 (!direct && cdiv(std::min(split_chunk(K, split, 64), K - split_chunk(K, split, 64) * (split - 1)), 64) <
                                 dma_min_steps(c.tile)))
                 continue;
+            Pack pk;
+            pk.a = copies && copy_a;
+            pk.b = copies && copy_b;
+            pk.k8 = cdiv(K, 8) * 8;
+            pk.n8 = cdiv(N, 8) * 8;
+            if (batch == 1 && place_copies(split_bytes(c.tile, split, M, N), M, &pk) > max_ws)
+                continue;
             const double us = launch_cost(c, M, N, K, batch, odd_a, odd_b, split, cu_count) +
                               (copies ? copy_cost(M, N, K, copy_a, copy_b, batch) : 0.0);
             if (us < best) {
@@ -596,18 +647,10 @@ void select_launch(int64_t M, int64_t N, int64_t K, const void *A, int64_t lda, 
         }
     }
     if (slot) {
-        const PlanCache::Launch made{M, N, K, batch, flags, from, *cfg};
+        const PlanCache::Launch made{M, N, K, batch, flags, max_ws, from, *cfg};
         std::lock_guard<std::mutex> hold(cache->lock);
         *slot = made;
     }
-}
-
-size_t workspace_bytes(int64_t M, int64_t N, int split)
-{
-    if (split <= 1)
-        return 0;
-    const int64_t ldw = cdiv(N, 4) * 4;
-    return (size_t)split * (size_t)M * (size_t)ldw * sizeof(float);
 }
 
 // Grid of `blocks` workgroups (blocks < 2^31): one dimension while the
@@ -830,16 +873,6 @@ struct Segment {
     int dp_rounds, sk_tiles, kt;  // persistent kernel: rounds of whole tiles, shared tiles, K steps per tile
 };
 
-// Operands copied into the workspace (pack16) so that the pipelined kernels
-// can run: A as M x k8 (leading dimension k8), B as k8 x n8 (leading
-// dimension n8), with k8 and n8 the K and N rounded up to multiples of 8 and
-// zero padding.  Offsets are bytes from the workspace base.
-struct Pack {
-    bool a = false, b = false;
-    int64_t k8 = 0, n8 = 0;
-    size_t a_off = 0, b_off = 0;
-};
-
 // Everything about a call that follows from the arguments on the host.
 struct Plan {
     int tile;
@@ -987,10 +1020,7 @@ int make_plan_with(int64_t M, int64_t N, int64_t K, const void *A, int64_t lda, 
     // packed operands follow the split partials in the workspace
     auto finish = [&]() {
         if (pk.a || pk.b) {
-            pk.a_off = (out->ws + 255) / 256 * 256;
-            const size_t a_bytes = pk.a ? (size_t)M * (size_t)pk.k8 * 2 : 0;
-            pk.b_off = (pk.a_off + a_bytes + 255) / 256 * 256;
-            out->ws = pk.b ? pk.b_off + (size_t)pk.k8 * (size_t)pk.n8 * 2 : pk.a_off + a_bytes;
+            out->ws = place_copies(out->ws, M, &pk);
             for (int i = 0; i < out->nseg; ++i) {
                 if (pk.a)
                     out->seg[i].p.A = (const uint16_t *)(uintptr_t)pk.a_off;
@@ -1007,16 +1037,11 @@ int make_plan_with(int64_t M, int64_t N, int64_t K, const void *A, int64_t lda, 
         return make_plan_with(M, N, K, A, lda, B, ldb, C, ldc, other, cu_count, pk, out);
     }
     if (split > 1) {
-        const size_t block = direct_block_bytes(cfg.tile);
-        if (combines(cfg.tile, split) && tiles <= kMaxSkGrid) {
-            // the last workgroup of each tile adds the partial blocks
-            add(0, tiles, split, kc, 0);
-            out->seg[0].reduce = 2;
-            out->ws = (size_t)tiles * (size_t)split * block;
-            return finish();
-        }
-        add(0, tiles, split, kc, 1);
-        out->ws = workspace_bytes(M, N, split);
+        const bool last_adds = combines_all(cfg.tile, split, M, N);
+        add(0, tiles, split, kc, last_adds ? 0 : 1);
+        if (last_adds)
+            out->seg[0].reduce = 2;   // the last workgroup of each tile adds the partial blocks
+        out->ws = split_bytes(cfg.tile, split, M, N);
         return finish();
     }
     add(0, tiles, 1, kc, 0);
@@ -1164,11 +1189,17 @@ struct CallPlan {
     size_t ws = 0;
 };
 
+// Whether a workspace of `ws` bytes after its prefix keeps a limit (0: none).
+bool within_limit(size_t ws, size_t limit) { return ws == 0 || limit == 0 || ws + kWsPrefix <= limit; }
+
 // Plan a call with K > 0 and M, N > 0 (arguments already checked): the
 // forced configuration, or the selected plan, banded or not.  limit: bytes a
-// workspace may have (0: any); a tile plan that needs more is returned as it
-// is, for the caller to refuse, and another launch is taken in its place only
-// within it.  Touches no GPU.
+// workspace may have (0: any).  The launch does not depend on it as long as it
+// fits; where only the tile plan fits, that runs, and a plan that needs more
+// is returned as it is, for the caller to refuse.  Another launch than the
+// tile plan needs at most what xgemm_run_noalloc's scratch holds, or what the
+// tile plan needs: so whatever that entry point accepts, it runs as xgemm_run
+// does.  Touches no GPU.
 int plan_call(int cu_count, int64_t M, int64_t N, int64_t K, const void *A, int64_t lda, const void *B, int64_t ldb,
               float *C, int64_t ldc, const xgemm_config *forced, CallPlan *cp, bool allow_sk = true, size_t limit = 0,
               PlanCache *cache = nullptr)
@@ -1181,7 +1212,6 @@ int plan_call(int cu_count, int64_t M, int64_t N, int64_t K, const void *A, int6
     }
     if (!allow_sk)
         band.body.stream_k = band.band.stream_k = 0;
-    int64_t limit_ws = limit > 0 ? (int64_t)limit - (int64_t)kWsPrefix : INT64_MAX;
     if (!forced && band.body.stream_k > 0) {
         // operands the persistent kernel cannot take as they are (alignment,
         // leading dimensions): the plan without it, banded or not
@@ -1215,15 +1245,17 @@ int plan_call(int cu_count, int64_t M, int64_t N, int64_t K, const void *A, int6
             return rc;
         cp->ws = cp->plan[i].ws > cp->ws ? cp->plan[i].ws : cp->ws;
     }
-    if (forced || cp->parts != 1 || band.body.stream_k > 0 || (int64_t)cp->ws > limit_ws)
+    if (forced || cp->parts != 1 || band.body.stream_k > 0)
         return XGEMM_OK;
     // one launch of a tile plan: another kernel where the model prefers it
     xgemm_config cfg = band.body;
-    select_launch(M, N, K, A, lda, 0, B, ldb, 0, 1, cp->ws > 0, cu_count, cache, &cfg);
+    const size_t max_ws = std::max(kScratchBytes - kWsPrefix, cp->ws);
+    select_launch(M, N, K, A, lda, 0, B, ldb, 0, 1, cp->ws > 0, max_ws, cu_count, cache, &cfg);
     if (cfg.tile != band.body.tile || cfg.split_k != band.body.split_k) {
         Plan other;
         if (make_plan(M, N, K, A, lda, B, ldb, C, ldc, cfg, cu_count, &other, true) == XGEMM_OK &&
-            other.tile == cfg.tile && (is_direct(cfg.tile) || other.seg[0].dma) && (int64_t)other.ws <= limit_ws) {
+            other.tile == cfg.tile && (is_direct(cfg.tile) || other.seg[0].dma) && other.ws <= max_ws &&
+            (within_limit(other.ws, limit) || !within_limit(cp->ws, limit))) {
             cp->plan[0] = other;
             cp->ws = other.ws;
         }
@@ -1425,7 +1457,7 @@ int run_batched(xgemm_ctx *h, int64_t batch, int64_t M, int64_t N, int64_t K, co
     xgemm_config cfg;
     select_config_batched(batch, M, N, K, h->cu_count, &cfg);
     if (h->ws_limit == 0 && !(h->persistent && use_persistent(M, N, K, h->cu_count, cfg, batch)))
-        select_launch(M, N, K, A, lda, sa, B, ldb, sb, batch, true, h->cu_count, h->plans, &cfg);
+        select_launch(M, N, K, A, lda, sa, B, ldb, sb, batch, true, SIZE_MAX, h->cu_count, h->plans, &cfg);
     Plan plan;
     rc = make_plan(M, N, K, A, lda, B, ldb, C, ldc, cfg, h->cu_count, &plan, false);
     if (rc != XGEMM_OK)

@@ -99,6 +99,71 @@ int kept()
     return found != 3;
 }
 
+// The plan xgemm_run_noalloc enqueues, or false where it refuses the call.
+bool noalloc(const Shape &s, CallPlan *cp)
+{
+    if (plan(s, true, kScratchBytes, nullptr, cp) != XGEMM_OK)
+        return false;
+    if (cp->ws + kWsPrefix > kScratchBytes && plan(s, false, kScratchBytes, nullptr, cp) != XGEMM_OK)
+        return false;
+    return cp->ws + kWsPrefix <= kScratchBytes;
+}
+
+// What a limit on the workspace changes: xgemm_run_noalloc takes a call
+// exactly if xgemm_run's plan fits its scratch, and then runs the same plan
+// (but for the persistent kernel's partial sums); a limit in general refuses
+// no call whose plan needs less.
+int limits()
+{
+    std::vector<Shape> all = shapes(3000);
+    // tile plans that fit the scratch where a deeper K split does not
+    for (Shape s : {Shape{201, 571, 37855, 37855, 571}, Shape{375, 357, 38245, 38245, 357},
+                    Shape{533, 177, 42183, 42183, 177}, Shape{515, 207, 41455, 41455, 207}})
+        all.push_back(s);
+    // decoding steps read in place, whose operand copies would not fit
+    const std::vector<Shape> in_place = {{93, 13489, 12508, 12508, 13489}, {16, 10377, 8657, 8657, 10377}};
+    all.insert(all.end(), in_place.begin(), in_place.end());
+    std::mt19937 gen(11);
+    for (int i = 0; i < 2000; ++i) {   // few outputs, long K
+        Shape s{128 + (int64_t)(gen() % 896), 128 + (int64_t)(gen() % 896), 8192 + (int64_t)(gen() % 57344), 0, 0};
+        s.lda = s.K;
+        s.ldb = s.N;
+        all.push_back(s);
+    }
+    int bad = 0, accepted = 0;
+    auto fail = [&](const Shape &s, const char *why) {
+        if (++bad < 10)
+            printf("%lld x %lld x %lld (lda %lld, ldb %lld): %s\n", (long long)s.M, (long long)s.N, (long long)s.K,
+                   (long long)s.lda, (long long)s.ldb, why);
+    };
+    for (const Shape &s : all) {
+        CallPlan run, na, cp;
+        plan(s, true, 0, nullptr, &run);
+        const bool took = noalloc(s, &na);
+        accepted += took;
+        if (run.plan[0].seg[0].sk && run.ws > 0)
+            plan(s, run.ws + kWsPrefix <= kScratchBytes, 0, nullptr, &run);
+        if (took != (run.ws + kWsPrefix <= kScratchBytes))
+            fail(s, took ? "taken, though xgemm_run's plan does not fit" : "refused, though xgemm_run's plan fits");
+        else if (took && !same(run, na))
+            fail(s, "another plan than xgemm_run's");
+        const size_t limit = run.ws + kWsPrefix;
+        plan(s, run.plan[0].seg[0].sk, limit, nullptr, &cp);
+        if (!same(run, cp))
+            fail(s, "another plan under the limit it keeps");
+        plan(s, true, 1, nullptr, &cp);
+        if (run.ws == 0 && cp.ws != 0)
+            fail(s, "needs a workspace under a limit, none without");
+    }
+    for (const Shape &s : in_place) {
+        CallPlan cp;
+        if (!noalloc(s, &cp))
+            fail(s, "refused");
+    }
+    printf("%d of %zu fit the scratch, %d wrong\n", accepted, all.size(), bad);
+    return bad != 0;
+}
+
 }  // namespace
 
 int main(int argc, char **argv)
@@ -108,5 +173,7 @@ int main(int argc, char **argv)
         return threads(atoi(argv[2]));
     if (!strcmp(what, "kept"))
         return kept();
+    if (!strcmp(what, "limits"))
+        return limits();
     return 2;
 }

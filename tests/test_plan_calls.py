@@ -1,5 +1,5 @@
 """What calls are planned as, where only a handle's state shows it: the table
-of selections under several threads.  The library's host code is compiled
+of selections under several threads, and limits on the workspace.  The library's host code is compiled
 alone and run on the CPU."""
 import os
 import subprocess
@@ -36,3 +36,10 @@ def test_threads_share_a_table(host, count):
 def test_both_plans_of_a_shape_are_kept(host):
     """With and without the persistent kernel: neither lookup evicts the other."""
     host("kept")
+
+
+def test_limits_on_the_workspace(host):
+    """xgemm_run_noalloc takes a call exactly if xgemm_run's plan fits the
+    static array, and then runs that plan; no limit refuses or changes a call
+    whose plan keeps it."""
+    host("limits")

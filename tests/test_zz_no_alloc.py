@@ -94,3 +94,28 @@ def test_noalloc_rejects_calls_beyond_the_scratch():
         assert torch.all(C[:M, :N] == 0.0) and torch.all(C[:, N:] == 5.0) and torch.all(C[M:] == 5.0)
     finally:
         xg.xgemm_destroy(h)
+
+
+@pytest.mark.parametrize("M,N,K", [(201, 571, 37855), (515, 207, 41455), (16, 10377, 8657)],
+                         ids=lambda v: str(v))
+def test_noalloc_at_the_scratch_limit(M, N, K):
+    """Where the static array decides: a K split one deeper than it holds, and
+    a decoding step read in place whose operand copies it could not hold.
+    Taken, with xgemm_run's bits."""
+    oracle.build(force=False)
+    A, B = wl.make_inputs(M, N, K, "bf16", "uniform", seed=M)
+    dA, dB = to_device(A, "bf16"), to_device(B, "bf16")
+    outs = [torch.full((M, N), float("nan"), dtype=torch.float32, device="cuda") for _ in range(2)]
+    h = xg.xgemm_create()
+    try:
+        s = torch.cuda.current_stream().cuda_stream
+        for fn, C in zip((xg.xgemm_run_noalloc, xg.xgemm_run), outs):
+            assert _call(fn, h, M, N, K, dA, dB, C, "bf16", s) == xg.XGEMM_OK, xg.xgemm_last_error(h)
+        torch.cuda.synchronize()
+        assert torch.equal(*outs)
+        rows = np.unique(np.linspace(0, M - 1, 16).astype(int))
+        C_ref, S = oracle.gemm_rows(A, B, "bf16", rows)
+        check_close(outs[0].cpu().numpy()[rows], C_ref, S, "noalloc %dx%dx%d" % (M, N, K))
+    finally:
+        torch.cuda.synchronize()
+        xg.xgemm_destroy(h)
