@@ -229,7 +229,8 @@ int xgemm_run_config(xgemm_handle_t h, int64_t M, int64_t N, int64_t K,
  * run in one launch without split-k; the pipelined path additionally needs
  * stride_a and stride_b multiples of 8.  Operands that miss the layout are copied into the
  * handle's workspace as in xgemm_run, one copy per problem (one in all for
- * a stride of 0), which needs batch times the operand's padded size.
+ * a stride of 0), which needs batch times the operand's padded size; or the
+ * register-direct kernel reads them in place where that is faster.
  * Errors as xgemm_run, plus XGEMM_ERR_INVALID_ARG for negative batch or
  * strides, overlapping outputs or batch > 2^31 - 1.
  */

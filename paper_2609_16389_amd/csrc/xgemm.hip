@@ -1422,6 +1422,128 @@ int launch_plan(xgemm_ctx *h, Plan plan, char *ws, int64_t M, int64_t N, int64_t
     return XGEMM_OK;
 }
 
+// Outputs of different problems must not overlap; every problem's matrices
+// must stay addressable.
+bool batch_args_ok(int64_t batch, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t sa, int64_t ldb, int64_t sb,
+                   int64_t ldc, int64_t sc)
+{
+    if (sc < (M - 1) * ldc + N)
+        return false;
+    const double last = (double)(batch - 1);
+    return last * sa + (double)M * lda <= 9.0e18 && last * sb + (double)K * ldb <= 9.0e18 &&
+           last * sc + (double)M * ldc <= 9.0e18 && batch <= 0x7fffffff;
+}
+
+// A batch of two or more problems: one launch over all their tiles.
+struct BatchPlan {
+    Plan plan;           // packed operands as byte offsets in the workspace
+    int64_t sa, sb;      // batch strides of the operands the launch reads
+    int64_t na, nb;      // copies of A and of B (one of an operand all problems share)
+    size_t ws;
+};
+
+// Plan `batch` > 1 problems with K > 0 and M, N > 0 (arguments already
+// checked) in the configuration cfg.  Touches no GPU.
+int plan_batched(int cu_count, bool persistent, int64_t batch, int64_t M, int64_t N, int64_t K, const void *A,
+                 int64_t lda, int64_t sa, const void *B, int64_t ldb, int64_t sb, const float *C, int64_t ldc,
+                 int64_t sc, const xgemm_config &cfg, BatchPlan *out)
+{
+    Plan &plan = out->plan;
+    int rc = make_plan(M, N, K, A, lda, B, ldb, C, ldc, cfg, cu_count, &plan, false);
+    if (rc != XGEMM_OK)
+        return rc;
+    out->ws = 0;
+    // Operands the pipelined kernel cannot read in place (for every problem:
+    // alignment, leading dimension, batch stride, N or K) are copied into the
+    // workspace, one copy per problem (a single one for a shared operand,
+    // stride 0), when that makes the pipelined kernel eligible.
+    const bool k_ok = K % 8 == 0;
+    Pack pk;
+    pk.a = !(k_ok && (uintptr_t)A % 16 == 0 && lda % 8 == 0 && sa % 8 == 0);
+    pk.b = !(k_ok && (uintptr_t)B % 16 == 0 && ldb % 8 == 0 && sb % 8 == 0 && N % 8 == 0);
+    if (!k_ok)
+        pk.a = pk.b = true;
+    pk.k8 = cdiv(K, 8) * 8;
+    pk.n8 = cdiv(N, 8) * 8;
+    out->na = sa == 0 ? 1 : batch;
+    out->nb = sb == 0 ? 1 : batch;
+    Plan packed;
+    if ((pk.a || pk.b) && !is_direct(plan.tile) &&
+        make_plan_with(M, N, K, A, lda, B, ldb, C, ldc, cfg, cu_count, pk, &packed) == XGEMM_OK &&
+        packed.seg[0].dma) {
+        const size_t a_bytes = pk.a ? (size_t)out->na * (size_t)M * (size_t)pk.k8 * 2 : 0;
+        pk.a_off = 0;
+        pk.b_off = (a_bytes + 255) / 256 * 256;
+        out->ws = pk.b ? pk.b_off + (size_t)out->nb * (size_t)pk.k8 * (size_t)pk.n8 * 2 : a_bytes;
+        plan = packed;
+        plan.pack = pk;
+        if (pk.a) {
+            plan.seg[0].p.A = (const uint16_t *)(uintptr_t)pk.a_off;
+            sa = sa == 0 ? 0 : M * pk.k8;
+        }
+        if (pk.b) {
+            plan.seg[0].p.B = (const uint16_t *)(uintptr_t)pk.b_off;
+            sb = sb == 0 ? 0 : pk.k8 * pk.n8;
+        }
+    } else {
+        plan.pack = pk = Pack{};
+    }
+    Segment &g = plan.seg[0];
+    if (plan.nseg != 1 || g.reduce != 0 || g.p.split != 1)
+        return XGEMM_ERR_INVALID_ARG;  // batched plans are single unsplit launches
+    if (g.grid * batch > 0x7fffffff)
+        return XGEMM_ERR_INVALID_ARG;
+    out->sa = sa;
+    out->sb = sb;
+    g.p.batch = (int)batch;
+    g.p.stride_a = sa;
+    g.p.stride_b = sb;
+    g.p.stride_c = sc;
+    // 16-byte loads need every problem's operands aligned, the persistent
+    // kernel's buffer stores every problem's C
+    g.p.vec_ab = g.p.vec_ab && (sa % 8 == 0) && (sb % 8 == 0);
+    g.vec_c = g.vec_c && (sc % 4 == 0);
+    g.dma = !is_direct(plan.tile) && dma_eligible(g.p, plan.tile, pk.b);
+    // the persistent kernel over the tiles of all problems, as xgemm_run
+    // takes it for one problem with as many tiles
+    const TileShape &t256 = kTiles[XGEMM_TILE_256x256];
+    if (persistent && !pk.a && !pk.b && g.dma && g.vec_c && use_persistent(M, N, K, cu_count, cfg, batch) &&
+        (int64_t)t256.bm * ldc * 4 < ((int64_t)1 << 32) &&
+        sk_schedule(g, (M / t256.bm) * (N / t256.bn) * batch, K / t256.bk, cu_count))
+        out->ws = sk_workspace(g);
+    else
+        g.grid *= batch;
+    return XGEMM_OK;
+}
+
+// The plan of a batched call: another launch in the selected tile plan's place
+// where the model prefers it, as for one problem (plan_call); no limit
+// changes it except that a tile plan that fits runs where the other does not.
+int plan_batched_call(int cu_count, bool persistent, int64_t batch, int64_t M, int64_t N, int64_t K, const void *A,
+                      int64_t lda, int64_t sa, const void *B, int64_t ldb, int64_t sb, const float *C, int64_t ldc,
+                      int64_t sc, size_t limit, PlanCache *cache, BatchPlan *out)
+{
+    xgemm_config tile;
+    select_config_batched(batch, M, N, K, cu_count, &tile);
+    auto with = [&](const xgemm_config &cfg, BatchPlan *bp) {
+        return plan_batched(cu_count, persistent, batch, M, N, K, A, lda, sa, B, ldb, sb, C, ldc, sc, cfg, bp);
+    };
+    if (!(persistent && use_persistent(M, N, K, cu_count, tile, batch))) {
+        xgemm_config cfg = tile;
+        select_launch(M, N, K, A, lda, sa, B, ldb, sb, batch, true, SIZE_MAX, cu_count, cache, &cfg);
+        // (fewer than 8 columns or K, or rows far apart: the kernel chosen does not apply)
+        if (cfg.tile != tile.tile && with(cfg, out) == XGEMM_OK && out->plan.tile == cfg.tile &&
+            (is_direct(cfg.tile) || out->plan.seg[0].dma)) {
+            BatchPlan plain;
+            if (within_limit(out->ws, limit) || with(tile, &plain) != XGEMM_OK || !within_limit(plain.ws, limit))
+                return XGEMM_OK;
+            *out = plain;
+            return XGEMM_OK;
+        }
+    }
+    return with(tile, out);
+}
+
 int run_batched(xgemm_ctx *h, int64_t batch, int64_t M, int64_t N, int64_t K, const void *A, int64_t lda,
                 int64_t sa, const void *B, int64_t ldb, int64_t sb, float *C, int64_t ldc, int64_t sc, int dtype,
                 void *stream)
@@ -1435,13 +1557,7 @@ int run_batched(xgemm_ctx *h, int64_t batch, int64_t M, int64_t N, int64_t K, co
         return XGEMM_OK;
     if (batch == 1)
         return run(h, M, N, K, A, lda, B, ldb, C, ldc, dtype, stream, nullptr);
-    // outputs of different problems must not overlap; every problem's
-    // matrices must stay addressable
-    if (sc < (M - 1) * ldc + N)
-        return XGEMM_ERR_INVALID_ARG;
-    const double last = (double)(batch - 1);
-    if (last * sa + (double)M * lda > 9.0e18 || last * sb + (double)K * ldb > 9.0e18 ||
-        last * sc + (double)M * ldc > 9.0e18 || batch > 0x7fffffff)
+    if (!batch_args_ok(batch, M, N, K, lda, sa, ldb, sb, ldc, sc))
         return XGEMM_ERR_INVALID_ARG;
     h->last_error[0] = '\0';
     hipStream_t s = (hipStream_t)stream;
@@ -1454,104 +1570,39 @@ int run_batched(xgemm_ctx *h, int64_t batch, int64_t M, int64_t N, int64_t K, co
         }
         return XGEMM_OK;
     }
-    xgemm_config cfg;
-    select_config_batched(batch, M, N, K, h->cu_count, &cfg);
-    if (h->ws_limit == 0 && !(h->persistent && use_persistent(M, N, K, h->cu_count, cfg, batch)))
-        select_launch(M, N, K, A, lda, sa, B, ldb, sb, batch, true, SIZE_MAX, h->cu_count, h->plans, &cfg);
-    Plan plan;
-    rc = make_plan(M, N, K, A, lda, B, ldb, C, ldc, cfg, h->cu_count, &plan, false);
+    BatchPlan bp;
+    rc = plan_batched_call(h->cu_count, h->persistent, batch, M, N, K, A, lda, sa, B, ldb, sb, C, ldc, sc,
+                           h->ws_limit, h->plans, &bp);
     if (rc != XGEMM_OK)
         return rc;
-    // Operands the pipelined kernel cannot read in place (for every problem:
-    // alignment, leading dimension, batch stride, N or K) are copied into the
-    // workspace, one copy per problem (a single one for a shared operand,
-    // stride 0), when that makes the pipelined kernel eligible.
-    const bool k_ok = K % 8 == 0;
-    Pack pk;
-    pk.a = !(k_ok && (uintptr_t)A % 16 == 0 && lda % 8 == 0 && sa % 8 == 0);
-    pk.b = !(k_ok && (uintptr_t)B % 16 == 0 && ldb % 8 == 0 && sb % 8 == 0 && N % 8 == 0);
-    if (!k_ok)
-        pk.a = pk.b = true;
-    pk.k8 = cdiv(K, 8) * 8;
-    pk.n8 = cdiv(N, 8) * 8;
-    const int64_t na = sa == 0 ? 1 : batch, nb = sb == 0 ? 1 : batch;
-    Plan packed;
-    if ((pk.a || pk.b) && !is_direct(plan.tile) &&
-        make_plan_with(M, N, K, A, lda, B, ldb, C, ldc, cfg, h->cu_count, pk, &packed) == XGEMM_OK &&
-        packed.seg[0].dma) {
-        const size_t a_bytes = pk.a ? (size_t)na * (size_t)M * (size_t)pk.k8 * 2 : 0;
-        pk.a_off = 0;
-        pk.b_off = (a_bytes + 255) / 256 * 256;
-        const size_t ws = pk.b ? pk.b_off + (size_t)nb * (size_t)pk.k8 * (size_t)pk.n8 * 2 : a_bytes;
-        if (packed.nseg != 1 || packed.seg[0].reduce != 0 || packed.seg[0].p.split != 1 ||
-            packed.seg[0].grid * batch > 0x7fffffff)
-            return XGEMM_ERR_INVALID_ARG;  // batched plans are single unsplit launches
-        rc = acquire_workspace(h, ws, s);
-        if (rc != XGEMM_OK)
-            return rc;
-        char *const w = ws_data(h->workspace);
-        const auto pa = pack_operand(A, lda, sa, M, K, w + pk.a_off, M, pk.k8, na);
-        const auto pb = pack_operand(B, ldb, sb, K, N, w + pk.b_off, pk.k8, pk.n8, nb);
+    if (bp.ws > 0 && (rc = acquire_workspace(h, bp.ws, s)) != XGEMM_OK)
+        return rc;
+    char *const base = bp.ws > 0 ? (char *)h->workspace : nullptr;
+    char *const w = base ? ws_data(base) : nullptr;
+    Segment &g = bp.plan.seg[0];
+    const Pack &pk = bp.plan.pack;
+    rc = XGEMM_OK;
+    if (pk.a || pk.b) {
+        const auto pa = pack_operand(A, lda, sa, M, K, w + pk.a_off, M, pk.k8, bp.na);
+        const auto pb = pack_operand(B, ldb, sb, K, N, w + pk.b_off, pk.k8, pk.n8, bp.nb);
         if ((e = launch_pack(pk.a ? &pa : nullptr, pk.b ? &pb : nullptr, s)) != hipSuccess) {
             set_error(h, "operand copy launch", e);
-            (void)release_workspace(h, s);
-            return XGEMM_ERR_HIP;
+            rc = XGEMM_ERR_HIP;
         }
-        plan = packed;
-        if (pk.a) {
-            plan.seg[0].p.A = (const uint16_t *)(w + pk.a_off);
-            sa = sa == 0 ? 0 : M * pk.k8;
-        }
-        if (pk.b) {
-            plan.seg[0].p.B = (const uint16_t *)(w + pk.b_off);
-            sb = sb == 0 ? 0 : pk.k8 * pk.n8;
-        }
-    } else {
-        pk = Pack{};
+        if (pk.a)
+            g.p.A = (const uint16_t *)(w + pk.a_off);
+        if (pk.b)
+            g.p.B = (const uint16_t *)(w + pk.b_off);
     }
-    Segment &g = plan.seg[0];
-    if (plan.nseg != 1 || g.reduce != 0 || g.p.split != 1)
-        return XGEMM_ERR_INVALID_ARG;  // batched plans are single unsplit launches
-    if (g.grid * batch > 0x7fffffff)
-        return XGEMM_ERR_INVALID_ARG;
-    g.p.batch = (int)batch;
-    g.p.stride_a = sa;
-    g.p.stride_b = sb;
-    g.p.stride_c = sc;
-    // 16-byte loads need every problem's operands aligned, the persistent
-    // kernel's buffer stores every problem's C
-    g.p.vec_ab = g.p.vec_ab && (sa % 8 == 0) && (sb % 8 == 0);
-    g.vec_c = g.vec_c && (sc % 4 == 0);
-    g.dma = !is_direct(plan.tile) && dma_eligible(g.p, plan.tile, pk.b);
-    // the persistent kernel over the tiles of all problems, as xgemm_run
-    // takes it for one problem with as many tiles
-    const TileShape &t256 = kTiles[XGEMM_TILE_256x256];
-    if (h->persistent && !pk.a && !pk.b && g.dma && g.vec_c && use_persistent(M, N, K, h->cu_count, cfg, batch) &&
-        (int64_t)t256.bm * ldc * 4 < ((int64_t)1 << 32) &&
-        sk_schedule(g, (M / t256.bm) * (N / t256.bn) * batch, K / t256.bk, h->cu_count)) {
-        const size_t ws = sk_workspace(g);
-        if (ws > 0 && (rc = acquire_workspace(h, ws, s)) != XGEMM_OK)
-            return rc;
-        char *const base = ws > 0 ? (char *)h->workspace : nullptr;
-        e = launch_sk(dtype, sk_params(g, (int *)base, base ? (float *)ws_data(base) : nullptr), s);
-        rc = XGEMM_OK;
+    if (rc == XGEMM_OK) {
+        e = g.sk ? launch_sk(dtype, sk_params(g, (int *)base, (float *)w), s)
+                 : launch_tile(bp.plan.tile, g.dma, dtype, g.p, (int)g.grid, s);
         if (e != hipSuccess) {
             set_error(h, "gemm launch", e);
             rc = XGEMM_ERR_HIP;
         }
-        if (ws > 0) {
-            const int rc2 = release_workspace(h, s);
-            rc = rc == XGEMM_OK ? rc2 : rc;
-        }
-        return rc;
     }
-    e = launch_tile(plan.tile, g.dma, dtype, g.p, (int)(g.grid * batch), s);
-    rc = XGEMM_OK;
-    if (e != hipSuccess) {
-        set_error(h, "gemm launch", e);
-        rc = XGEMM_ERR_HIP;
-    }
-    if (pk.a || pk.b) {
+    if (bp.ws > 0) {
         const int rc2 = release_workspace(h, s);
         rc = rc == XGEMM_OK ? rc2 : rc;
     }

@@ -164,6 +164,49 @@ int limits()
     return bad != 0;
 }
 
+// Batched calls: a limit changes no plan that keeps it and refuses none that
+// needs less; a launch whose kernel does not apply (fewer than 8 columns or
+// K, rows far apart) leaves the tile plan's as it was.
+int batches()
+{
+    std::mt19937 gen(13);
+    int bad = 0, replaced = 0, apply = 0;
+    for (int i = 0; i < 4000; ++i) {
+        auto size = [&](double lo, double hi) {
+            return (int64_t)exp(std::uniform_real_distribution<double>(log(lo), log(hi))(gen));
+        };
+        const int64_t L = size(2, 129), M = size(1, 1025), N = i % 5 == 0 ? size(1, 8) : size(1, 1025),
+                      K = i % 7 == 0 ? size(1, 8) : size(1, 1025);
+        const int64_t pad = i % 3 == 0 ? 3 : 0;
+        const int64_t lda = i % 11 == 0 ? (int64_t)1 << 28 : K + pad, ldb = N + pad;
+        const int64_t sa = M * lda, sb = K * ldb, sc = M * N;
+        const uintptr_t base = 1 << 20;
+        xgemm_config tile;
+        select_config_batched(L, M, N, K, kCUs, &tile);
+        BatchPlan t, got, under;
+        auto call = [&](size_t limit, BatchPlan *bp) {
+            return plan_batched_call(kCUs, true, L, M, N, K, (void *)base, lda, sa, (void *)base, ldb, sb,
+                                     (float *)base, N, sc, limit, nullptr, bp);
+        };
+        plan_batched(kCUs, true, L, M, N, K, (void *)base, lda, sa, (void *)base, ldb, sb, (float *)base, N, sc, tile,
+                     &t);
+        const bool ok = call(0, &got) == XGEMM_OK && call(got.ws + kWsPrefix, &under) == XGEMM_OK;
+        replaced += got.plan.tile != t.plan.tile;
+        apply += !(N < 8 || K < 8 || lda > ((int64_t)1 << 27));
+        const bool general = !got.plan.seg[0].dma && !got.plan.seg[0].sk && !is_direct(got.plan.tile);
+        const bool kept = got.plan.tile == t.plan.tile && got.plan.seg[0].p.group_m == t.plan.seg[0].p.group_m;
+        if (!ok || under.plan.tile != got.plan.tile || under.ws != got.ws || (general && !kept) ||
+            ((N < 8 || K < 8) && is_direct(got.plan.tile))) {
+            if (++bad < 10)
+                printf("%lld of %lld x %lld x %lld, lda %lld: tile %d, under its own limit %d; the tile plan's %d\n",
+                       (long long)L, (long long)M, (long long)N, (long long)K, (long long)lda, got.plan.tile,
+                       under.plan.tile, t.plan.tile);
+        }
+    }
+    printf("%d of 4000 replaced, %d wrong\n", replaced, bad);
+    return bad != 0 || replaced < 1000 || apply < 1000;
+}
+
 }  // namespace
 
 int main(int argc, char **argv)
@@ -175,5 +218,7 @@ int main(int argc, char **argv)
         return kept();
     if (!strcmp(what, "limits"))
         return limits();
+    if (!strcmp(what, "batches"))
+        return batches();
     return 2;
 }

@@ -135,6 +135,32 @@ def test_batched_parity(shape):
 
 
 @pytest.mark.gpu
+def test_batched_under_a_workspace_limit():
+    """A limit on the workspace does not refuse a batch that needs none (its
+    tile plan would copy both operands)."""
+    import torch
+    from gpu_util import check_close, to_device
+    L, M, N, K = 3, 300, 201, 1000
+    oracle.build(force=False)
+    A, B = wl.make_inputs(M, N, K, "bf16", "normal", seed=5)
+    C_ref, S = oracle.gemm(A, B, "bf16")
+    dA, dB = (torch.stack([to_device(x, "bf16")] * L) for x in (A, B))
+    C = torch.full((L, M, N), float("nan"), device="cuda")
+    h = xg.xgemm_create()
+    try:
+        assert xg.xgemm_set_workspace_limit(h, 4096) == xg.XGEMM_OK
+        rc = xg.xgemm_run_strided_batched(h, L, M, N, K, dA.data_ptr(), K, M * K, dB.data_ptr(), N, K * N, C.data_ptr(),
+                                          N, M * N, xg.XGEMM_BF16, torch.cuda.current_stream().cuda_stream)
+        assert rc == xg.XGEMM_OK, xg.xgemm_last_error(h)
+        torch.cuda.synchronize()
+        for b in range(L):
+            check_close(C[b].cpu().numpy(), C_ref, S, "batched under a limit, problem %d" % b)
+    finally:
+        torch.cuda.synchronize()
+        xg.xgemm_destroy(h)
+
+
+@pytest.mark.gpu
 def test_infinities_stay_in_their_rows():
     """Zeroed lanes past K and clamped rows must not meet infinities of other
     rows: one infinite element of A reaches its own row only."""

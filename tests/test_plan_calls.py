@@ -43,3 +43,9 @@ def test_limits_on_the_workspace(host):
     static array, and then runs that plan; no limit refuses or changes a call
     whose plan keeps it."""
     host("limits")
+
+
+def test_batched_plans(host):
+    """The same of batched calls; and a launch whose kernel does not apply
+    leaves the selected tile plan as it was."""
+    host("batches")
