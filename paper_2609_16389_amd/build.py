@@ -34,15 +34,33 @@ def build(verbose: bool = False) -> str:
     return LIB
 
 
+def fastcall_tag() -> str:
+    """What the extension has to be built for: it reads torch's tensors by
+    their C++ layout."""
+    import sys
+
+    import torch
+    return "xgemm fastcall, Python %d.%d, torch %s" % (sys.version_info[0], sys.version_info[1], torch.__version__)
+
+
+def fastcall_is_current() -> bool:
+    """Whether the extension is there and built for this Python and torch."""
+    if not os.path.exists(FAST_LIB):
+        return False
+    with open(FAST_LIB, "rb") as f:
+        return fastcall_tag().encode() + b"\0" in f.read()
+
+
 def build_fastcall(verbose: bool = False) -> str:
-    """Compile the Python extension against torch's headers (host code only)."""
+    """Compile the Python extension against Python's and torch's headers (host
+    code only)."""
     import sysconfig
 
     import torch
     root = os.path.dirname(torch.__file__)
     tmp = FAST_LIB + ".tmp%d" % os.getpid()
     cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__=1",
-           "-DUSE_ROCM=1", "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI,
+           "-DUSE_ROCM=1", '-DXGEMM_FASTCALL_TAG="%s"' % fastcall_tag(), "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI,
            "-I" + os.path.join(root, "include"), "-I" + os.path.join(root, "include", "torch", "csrc", "api", "include"),
            "-I" + sysconfig.get_paths()["include"], "-I/opt/rocm/include", FAST_SRC, "-o", tmp,
            "-L" + os.path.join(root, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"]
@@ -54,7 +72,7 @@ def build_fastcall(verbose: bool = False) -> str:
 
 
 def is_stale() -> bool:
-    if not os.path.exists(LIB) or not os.path.exists(FAST_LIB):
+    if not os.path.exists(LIB) or not fastcall_is_current():
         return True
     t = os.path.getmtime(LIB)
     return any(os.path.getmtime(d) > t for d in DEPS) or os.path.getmtime(FAST_SRC) > os.path.getmtime(FAST_LIB)

@@ -228,7 +228,8 @@ PyMethodDef methods[] = {
     {nullptr, nullptr, 0, nullptr},
 };
 
-PyModuleDef module = {PyModuleDef_HEAD_INIT, "_fastcall", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
+// (the module's docstring says what it was built for: see build.py)
+PyModuleDef module = {PyModuleDef_HEAD_INIT, "_fastcall", XGEMM_FASTCALL_TAG, -1, methods, nullptr, nullptr, nullptr, nullptr};
 
 }  // namespace
 

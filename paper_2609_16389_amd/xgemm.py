@@ -6,8 +6,10 @@ for device memory and streams; ``gemm`` reads their pointers, strides and the
 current stream and calls ``xgemm_run``.  Every entry point is bound with
 ctypes; the ones on a program's hot path are called through ``_fastcall`` (the
 same library functions, without ctypes' argument conversion) when their
-arguments are of the plain kind.  There is no fallback path: if
-``libxgemm.so`` or ``_fastcall.so`` is missing the import of this module fails.
+arguments are of the plain kind.  There is no fallback path for the library:
+if ``libxgemm.so`` is missing the import of this module fails.  Without
+``_fastcall.so``, or with one built for another torch, it warns and makes
+every call through ctypes: the same results, some 6 us more host time a call.
 """
 from __future__ import annotations
 
@@ -126,7 +128,18 @@ if not os.path.exists(_LIB_PATH):
 
 lib = ctypes.CDLL(_LIB_PATH)
 
-from paper_2609_16389_amd import _fastcall  # noqa: E402
+from paper_2609_16389_amd import build as _build  # noqa: E402
+
+if _build.fastcall_is_current():
+    from paper_2609_16389_amd import _fastcall  # noqa: E402
+else:
+    import warnings
+    warnings.warn("_fastcall.so is not built for this Python and torch (run python -m paper_2609_16389_amd.build): "
+                  "calls go through ctypes", RuntimeWarning, stacklevel=2)
+
+    class _fastcall:
+        """Declines every call."""
+        bind = run = run_noalloc = gemm = bmm = gemv = staticmethod(lambda *args: None)
 
 _i64, _i32, _p = ctypes.c_int64, ctypes.c_int, ctypes.c_void_p
 _handle_t = ctypes.c_void_p

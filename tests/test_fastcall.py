@@ -1,5 +1,10 @@
 """The native call path of the Python binding: it takes plain GPU tensors and
 integers only, declines everything else, and gives what the ctypes path gives."""
+import os
+import shutil
+import subprocess
+import sys
+
 import pytest
 import torch
 
@@ -19,6 +24,31 @@ def test_declines_what_is_not_plain():
     # plain integers reach the library
     assert _fastcall.run(None, 1, 1, 1, None, 1, None, 1, None, 1, 0, None) == xg.XGEMM_ERR_INVALID_ARG
     assert xg.xgemm_run_noalloc(None, 1, 1, 1, None, 1, None, 1, None, 1, 0, None) == xg.XGEMM_ERR_INVALID_ARG
+
+
+@pytest.mark.parametrize("kind", ["missing", "other_torch"])
+def test_import_without_a_matching_extension(kind, tmp_path):
+    """The extension is an addition: without one built for this torch the
+    module warns, loads, and calls the library through ctypes."""
+    pkg = os.path.dirname(xg.__file__)
+    copy = tmp_path / "paper_2609_16389_amd"
+    shutil.copytree(pkg, copy, ignore=shutil.ignore_patterns("__pycache__", "csrc"))
+    ext = copy / "_fastcall.so"
+    if kind == "missing":
+        ext.unlink()
+    else:
+        tag = b"torch " + torch.__version__.encode()
+        data = ext.read_bytes()
+        assert tag in data
+        ext.write_bytes(data.replace(tag, b"torch 0" + tag[7:]))
+    code = ("import warnings\nwith warnings.catch_warnings(record=True) as w:\n"
+            "    warnings.simplefilter('always')\n    from paper_2609_16389_amd import xgemm as xg\n"
+            "assert any('_fastcall' in str(x.message) for x in w)\n"
+            "assert xg.xgemm_run(None, 1, 1, 1, None, 1, None, 1, None, 1, 0, None) == xg.XGEMM_ERR_INVALID_ARG\n"
+            "assert '_fastcall.so' not in open('/proc/self/maps').read()\n")
+    r = subprocess.run([sys.executable, "-c", code], cwd=tmp_path, env={**os.environ, "PYTHONPATH": str(tmp_path)},
+                       capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, r.stderr
 
 
 @pytest.mark.gpu
