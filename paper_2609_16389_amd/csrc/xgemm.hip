@@ -781,18 +781,41 @@ bool direct_eligible(const GemmParams &p, int bm)
            (64 * p.ldb + p.N) * 2 < ((int64_t)1 << 32);
 }
 
-// Streaming loads of B: where one row of blocks reads it once and it is too
-// large to be found again in the last-level cache (256 MB) by a later call.
-// 16 x 14336 x 4096 (117 MB) 25.4 against 27.9 us, 16 x 14336 x 16384 84.7
-// against 91.7; but 4 x 10736 x 3656 (78 MB), called again before other data
-// has replaced it, 17.6 against 15.7 for ordinary loads.
-constexpr double kStreamBytes = 96.0e6;
+// Streaming loads of B, which one row of blocks reads once.  They help where B
+// comes from HBM, but keep it out of the last-level cache (256 MiB), where a
+// call that follows with the same B would find it.  us with streaming /
+// ordinary loads at 16 rows, B rotating over 1.2 GB (as a decoding step's
+// weights do) and the same B again; and of 128 x 128 tiles through LDS:
+//                        rotating             again
+//    8192 x  4096  67 MB 19.9 / 20.3          18.4 / 15.3
+//   10240 x  4096  84 MB 21.4 / 22.2          20.1 / 17.2
+//   12288 x  4096 101 MB 22.7 / 23.6   27.0   21.8 / 19.3   22.4
+//   14336 x  4096 117 MB 24.8 / 26.1   28.5   23.1 / 21.8   24.6
+//   16384 x  4096 134 MB 27.0 / 29.7   32.1   25.6 / 23.8   27.7
+//   14336 x  5120 147 MB 29.5 / 31.2   33.3   28.9 / 25.9   28.5
+//   14336 x  8192 235 MB 43.9 / 46.8   47.9   43.9 / 38.7   40.4
+//   14336 x  9216 264 MB 48.4 / 51.8   52.7   48.7 / 44.4   44.9
+//   14336 x 10240 294 MB 53.6 / 57.1   58.4   54.1 / 53.3   57.0
+//   14336 x 12288 352 MB 63.3 / 67.7   68.6   64.3 / 69.7   70.7
+// The lines: up to 96 MB a rotating call gains 2-4% and one on its own B loses
+// 16-45%; from there to 140 MB, and above 280 MB, streaming is ahead of the
+// tiles either way and 4-9% faster on rotating weights; between, a call on its
+// own B would fall behind the tiles.  Only where rows of B are whole cache
+// lines: a line that two workgroups share is fetched twice when streamed
+// (14656 x 7168 in rows of 14664, 210 MB, rotating 42.4 / 40.0, again 41.1 /
+// 34.5; 14336 x 12288 in rows of 14344 67.7 / 64.7, 70.1 / 67.2).
+bool streams_b(const GemmParams &p)
+{
+    const double bytes = 2.0 * (double)p.N * (double)p.K;
+    return p.tiles_m == 1 && p.batch == 1 && (uintptr_t)p.B % 128 == 0 && p.ldb % 64 == 0 &&
+           (bytes > 280.0e6 || (bytes > 96.0e6 && bytes < 140.0e6));
+}
 
 template <int FM, int NV, int WN, int KW>
 hipError_t launch_direct(int dtype, GemmParams p, int grid, hipStream_t s)
 {
     p.grid = grid;
-    const bool nt = FM == 1 && p.tiles_m == 1 && p.batch == 1 && 2.0 * (double)p.N * (double)p.K > kStreamBytes;
+    const bool nt = FM == 1 && streams_b(p);
     auto go = [&](auto dt, auto stream) {
         hipLaunchKernelGGL(
             (xgemm_dev::gemm_kernel_direct<FM, NV, WN, KW, decltype(dt)::value, decltype(stream)::value>),

@@ -207,6 +207,32 @@ int batches()
     return bad != 0 || replaced < 1000 || apply < 1000;
 }
 
+// Which register-direct launches of a 16-row block stream B: its size, and
+// rows that are whole cache lines.
+int streams()
+{
+    struct {
+        int64_t M, N, K, ldb;
+        uintptr_t B;
+        bool on;
+    } const cases[] = {
+        {16, 14336, 4096, 14336, 1 << 20, true},     {5, 8192, 6001, 8192, 1 << 20, true},
+        {16, 14336, 4096, 14344, 1 << 20, false},    {16, 14336, 4096, 14336, (1 << 20) + 16, false},
+        {16, 14336, 12288, 14336, 1 << 20, true},    {16, 14336, 12288, 14339, 1 << 20, false},
+        {16, 14336, 8192, 14336, 1 << 20, false},    {16, 10240, 4096, 10240, 1 << 20, false},
+        {17, 14336, 4096, 14336, 1 << 20, false},
+    };
+    int bad = 0;
+    for (const auto &c : cases) {
+        CallPlan cp;
+        const xgemm_config cfg{XGEMM_DIRECT_16x128, 2, 4, 0};
+        bad += plan_call(kCUs, c.M, c.N, c.K, (void *)(1 << 20), c.K, (void *)c.B, c.ldb, (float *)(1 << 20), c.N, &cfg,
+                         &cp) != XGEMM_OK || cp.plan[0].tile != cfg.tile || streams_b(cp.plan[0].seg[0].p) != c.on;
+    }
+    printf("%d wrong\n", bad);
+    return bad != 0;
+}
+
 }  // namespace
 
 int main(int argc, char **argv)
@@ -220,5 +246,7 @@ int main(int argc, char **argv)
         return limits();
     if (!strcmp(what, "batches"))
         return batches();
+    if (!strcmp(what, "streams"))
+        return streams();
     return 2;
 }

@@ -174,6 +174,26 @@ def test_infinities_stay_in_their_rows():
         assert torch.all(torch.isinf(C[M - 1])) and torch.all(C[:M - 1] == K), tile
 
 
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", ["bf16", "fp16"])
+@pytest.mark.parametrize("split", [1, 2])
+def test_streaming_variant(dtype, split):
+    """B of 98 MB in rows of whole cache lines, read with streaming loads:
+    ragged rows, and a partial slab and vector of K."""
+    import torch
+    from gpu_util import check_close
+    M, N, K = 5, 8192, 6001
+    oracle.build(force=False)
+    A, B = wl.make_inputs(M, N, K, dtype, "uniform", K)
+    C_ref, S = oracle.gemm(A, B, dtype)
+    out = torch.full((M, N), float("nan"), device="cuda")
+    b = torch.from_numpy(B.view(np.int16)).cuda().view(torch.bfloat16 if dtype == "bf16" else torch.float16)
+    assert b.data_ptr() % 128 == 0 and 96e6 < 2 * N * K < 140e6
+    xg.gemm(_operand(A, dtype, 0), b, out=out, config=_cfg(xg.XGEMM_DIRECT_16x128, split))
+    torch.cuda.synchronize()
+    check_close(out.cpu().numpy(), C_ref, S, "streaming %s split %d" % (dtype, split))
+
+
 # (M, N, K, split) with partial blocks added by the last workgroup of a tile:
 # two ranges and the most, one tile and several, ragged rows and columns
 COMBINED = [(1, 8, 512, 2), (16, 300, 1101, 4), (70, 136, 2000, 3), (65, 257, 4160, 4)]

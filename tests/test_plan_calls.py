@@ -49,3 +49,8 @@ def test_batched_plans(host):
     """The same of batched calls; and a launch whose kernel does not apply
     leaves the selected tile plan as it was."""
     host("batches")
+
+
+def test_streaming_loads_of_b(host):
+    """By B's size and only over rows that are whole cache lines."""
+    host("streams")
