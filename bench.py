@@ -383,18 +383,29 @@ def bench_gemv(args, w):
 SWEEP_MAX_WORKGROUPS = 4096  # configurations with more workgroups than this are not swept
 
 
+LAUNCH_SPLITS = (1, 2, 3, 4, 6, 8, 12, 16, 24, 32)  # K splits of the launches beside the tile plans
+
+
 def sweep_candidates(M: int, N: int, K: int, selected: tuple, xg) -> list:
     """(tile, split) pairs the sweep times for one shape: every tile with
-    split-k 1, 2, 4, 8 and 16 where each split keeps 3 K steps and the launch
-    has at most SWEEP_MAX_WORKGROUPS workgroups, plus the selected one."""
+    split-k 1, 2, 4, 8 and 16 where each split keeps 3 K steps, the wave-pair
+    128 x 128 tile (4 steps) and every register-direct block (256 of K) with
+    the splits xgemm_run considers for them, where the launch has at most
+    SWEEP_MAX_WORKGROUPS workgroups, plus the selected one."""
     out = {tuple(selected)}
-    for tile in range(xg.XGEMM_TILE_COUNT):
+    launches = [xg.XGEMM_TILE_128x128_K2] + list(range(xg.XGEMM_DIRECT_16x128, xg.XGEMM_DIRECT_END))
+    for tile in list(range(xg.XGEMM_TILE_COUNT)) + launches:
         bm, bn, bk, _ = xg.xgemm_tile_info(tile)
-        for split in (1, 2, 4, 8, 16):
-            if split > 1 and K // split < 3 * bk:
+        least = 3 * bk if tile < xg.XGEMM_TILE_COUNT else 4 * bk
+        for split in LAUNCH_SPLITS if tile in launches else (1, 2, 4, 8, 16):
+            if split > 1 and K // split < least:
                 continue
             if -(-M // bm) * -(-N // bn) * split > SWEEP_MAX_WORKGROUPS:
                 continue
+            if tile in launches:
+                cfg = xg.xgemm_config(tile=tile, split_k=split, group_m=4, stream_k=0)
+                if xg.xgemm_kernel_family(M, N, K, 1 << 20, K, 1 << 20, N, cfg) == xg.XGEMM_KERNEL_GENERAL:
+                    continue
             out.add((tile, split))
     return sorted(out)
 
@@ -419,6 +430,9 @@ def sweep_shape(M: int, N: int, K: int, dtype: str = "bf16", rounds: int = 5) ->
     cu = torch.cuda.get_device_properties(0).multi_processor_count
     sel = xg.xgemm_select_config(M, N, K, code, cu)
     band = xg.xgemm_select_band(M, N, K, code, cu)
+    if band.axis == xg.XGEMM_BAND_NONE and not band.body.stream_k:
+        # one launch: the tile plan's, or the one xgemm_run takes in its place
+        sel = xg.xgemm_launch_config(M, N, K, A.data_ptr(), K, B.data_ptr(), N, cu)
     runs = []
     if band.axis != xg.XGEMM_BAND_NONE:
         def call_band():
@@ -535,6 +549,10 @@ def main():
     plan = xg.xgemm_select_plan(w.M, w.N, w.K, code, torch.cuda.get_device_properties(dev).multi_processor_count,
                                 0 if args.no_persistent else 1)
     cfg = plan.body  # the whole call's configuration, or the body's when C is cut in two
+    launch = xg.xgemm_launch_config(w.M, w.N, w.K, A.data_ptr(), w.K, B.data_ptr(), w.N,
+                                    torch.cuda.get_device_properties(dev).multi_processor_count)
+    if plan.axis == xg.XGEMM_BAND_NONE and not plan.body.stream_k and not launch.stream_k:
+        cfg = launch  # what xgemm_run enqueues in place of a single tile plan
     kernel_family = xg.xgemm_kernel_family(w.M, w.N, w.K, A.data_ptr(), w.K, B.data_ptr(), w.N, cfg)
 
     def step():
@@ -640,8 +658,8 @@ def main():
                 else "synthetic (seeded normal(0,%g), seed %d)" % (w.param, w.seed),
         "config": dict({"workload": w.name, "M": w.M, "N": w.N, "K": w.K, "out": "fp32",
                         "tile": cfg.tile, "split_k": cfg.split_k,
-                        "kernel": "persistent" if kernel_family == xg.XGEMM_KERNEL_PERSISTENT else
-                        "pipelined" if kernel_family == xg.XGEMM_KERNEL_PIPELINED else "general"},
+                        "kernel": {xg.XGEMM_KERNEL_PERSISTENT: "persistent", xg.XGEMM_KERNEL_PIPELINED: "pipelined",
+                                   xg.XGEMM_KERNEL_DIRECT: "direct"}.get(kernel_family, "general")},
                        **({} if plan.axis == xg.XGEMM_BAND_NONE else {"band": {
                            "axis": "columns" if plan.axis == xg.XGEMM_BAND_COLUMNS else "rows",
                            "body_extent": plan.extent, "tile": plan.band.tile,
