@@ -207,6 +207,21 @@ int batches()
     return bad != 0 || replaced < 1000 || apply < 1000;
 }
 
+// The launch a batch takes: L, M, N, K, the pad of A's rows, one B for all.
+int batch_route(char **v)
+{
+    const int64_t L = atoll(v[0]), M = atoll(v[1]), N = atoll(v[2]), K = atoll(v[3]), lda = K + atoll(v[4]);
+    const uintptr_t base = 1 << 20;
+    BatchPlan bp;
+    if (plan_batched_call(kCUs, true, L, M, N, K, (void *)base, lda, M * lda, (void *)base, N, atoi(v[5]) ? 0 : K * N,
+                          (float *)base, N, M * N, 0, nullptr, &bp) != XGEMM_OK)
+        return 1;
+    const Segment &g = bp.plan.seg[0];
+    printf("%s\n", is_direct(bp.plan.tile) ? "direct" : g.sk ? "persistent" : !g.dma ? "general" :
+                   bp.plan.pack.a || bp.plan.pack.b ? "copied" : "pipelined");
+    return 0;
+}
+
 // Which register-direct launches of a 16-row block stream B: its size, and
 // rows that are whole cache lines.
 int streams()
@@ -246,6 +261,8 @@ int main(int argc, char **argv)
         return limits();
     if (!strcmp(what, "batches"))
         return batches();
+    if (!strcmp(what, "batch_route") && argc == 8)
+        return batch_route(argv + 2);
     if (!strcmp(what, "streams"))
         return streams();
     return 2;

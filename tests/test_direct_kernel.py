@@ -79,13 +79,21 @@ def test_dispatch():
     for shape in [(4096, 4096, 4096), (8192, 8192, 8192), (6144, 6144, 6144), (1024, 1024, 65536)]:
         c, b = launch(*shape), xg.xgemm_select_band(*shape, xg.XGEMM_BF16, 256)
         assert (c.tile, c.split_k, c.stream_k) == (b.body.tile, b.body.split_k, b.body.stream_k), shape
-    waves = dict(zip(DIRECT, (8, 8, 8, 4, 2, 1, 1)))
+    # partial sums per element and K range: one per wave that takes slabs of its own
+    chains = dict(zip(DIRECT, (8, 8, 8, 4, 2, 1, 1)))
+    chains.update({xg.XGEMM_TILE_256x256: 1, xg.XGEMM_TILE_256x128: 2, xg.XGEMM_TILE_128x128: 1, K2: 2})
     rng = np.random.default_rng(5)
-    for _ in range(200):
-        M, N, K = (int(2 ** rng.uniform(0, 12)) for _ in range(3))
-        c, s = launch(M, N, K), xg.xgemm_select_config(M, N, K, xg.XGEMM_BF16, 256)
-        if c.tile in DIRECT:
-            assert c.split_k * waves[c.tile] >= s.split_k
+    # (the first two replace splits of the 256 x 128 tile, whose wave pairs split K too)
+    shapes = [(186, 7641, 6040), (166, 7695, 6627)]
+    shapes += [[int(2 ** rng.uniform(0, top)) for top in ((12, 12, 12), (10, 10, 16))[i % 2]] for i in range(3000)]
+    replaced = {}
+    for M, N, K in shapes:
+        b = xg.xgemm_select_band(M, N, K, xg.XGEMM_BF16, 256)
+        c, s = launch(M, N, K), b.body
+        if b.axis == xg.XGEMM_BAND_NONE and c.tile != s.tile and s.split_k > 1:
+            replaced[s.tile] = replaced.get(s.tile, 0) + 1
+            assert c.split_k * chains[c.tile] >= s.split_k * chains[s.tile], (M, N, K)
+    assert replaced[xg.XGEMM_TILE_256x128] > 0 and replaced[xg.XGEMM_TILE_128x128] >= 100, replaced
 
 
 def _operand(bits, dtype, pad):
@@ -116,11 +124,14 @@ def test_parity(tile, case, dtype):
     assert np.all(got[:, N:] == 7.0)
 
 
+# batches that take the direct kernel (tests/test_plan_calls.py checks it)
+BATCHES = [(5, 70, 264, 64), (3, 33, 137, 129), (40, 200, 72, 200)]
+
+
 @pytest.mark.gpu
-@pytest.mark.parametrize("shape", [(5, 70, 264, 64), (3, 33, 137, 129), (40, 200, 72, 200)],
-                         ids=lambda s: "x".join(map(str, s)))
+@pytest.mark.parametrize("shape", BATCHES, ids=lambda s: "x".join(map(str, s)))
 def test_batched_parity(shape):
-    """Batches that take the direct kernel: every problem's block edges."""
+    """Every problem's block edges."""
     import torch
     from gpu_util import check_close, to_device
     L, M, N, K = shape

@@ -116,9 +116,14 @@ def test_every_config_is_bit_identical():
         assert np.array_equal(y, base), "rows=%d unroll=%d" % (r, u)
 
 
+@pytest.mark.parametrize("M", [300, 1100])
 @pytest.mark.parametrize("a_offset,lda,x_offset", [(1, None, 0), (0, 5003, 0), (0, None, 1), (2, 5001, 3)])
-def test_unaligned_layouts_match_the_vector_path(a_offset, lda, x_offset):
-    M, K = 300, 5000
+def test_unaligned_layouts_match_the_vector_path(a_offset, lda, x_offset, M):
+    """Fewer than two workgroups per CU (300 rows) read any layout 16 bytes at a
+    time, more (1100 rows) an unaligned one 4 bytes at a time."""
+    K = 5000
+    cfg = xg.xgemv_select_config(M, K, 256)
+    assert cfg.split_k == 1 and (-(-M // cfg.rows) < 512) == (M == 300)
     A, x = wl.make_gemv_inputs(M, K, "uniform", 10)
     y_ref, s = oracle.gemv(A, x)
     aligned = run(A, x)

@@ -144,8 +144,10 @@ def test_partial_k_step_in_last_split(tile, split):
                 "partial last split tile %d split %d" % (tile, split))
 
 
-# Layouts the pipelined kernels cannot read in place:
-# the library copies the operand(s) into its workspace, zero-padded
+# Layouts the pipelined kernels cannot read in place: under a tile's
+# configuration the library copies the operand(s) into its workspace,
+# zero-padded.  (Called without one, problems this small are read in place by
+# the register-direct kernel.)
 PACKED_CASES = {
     "n_odd": ((1000, 1001, 1024), {}),
     "k_odd": ((1000, 1000, 1003), {}),
@@ -156,23 +158,36 @@ PACKED_CASES = {
 }
 
 
+def _copied(M, N, K, cfg, lda=None, ldb=None, offset=0):
+    """Which operands the launch under this configuration copies (1: A, 2: B,
+    3: both); cfg None: the launch xgemm_run makes."""
+    lda, ldb, base = lda or K, ldb or N, (1 << 20) + 2 * offset
+    if cfg is None:
+        cfg = xg.xgemm_launch_config(M, N, K, base, lda, base, ldb, 256)
+    info = xg.xgemm_trace_plan(M, N, K, base, lda, base, ldb, 1 << 20, N, cfg, 256, 0)
+    assert not info.packed or info.family == xg.XGEMM_KERNEL_PIPELINED
+    return info.packed
+
+
 @pytest.mark.parametrize("name", sorted(PACKED_CASES))
 @pytest.mark.parametrize("dtype", ["bf16", "fp16"])
 def test_packed_operands(name, dtype):
     (M, N, K), kw = PACKED_CASES[name]
     lda, ldb, off = kw.get("lda", K), kw.get("ldb", N), kw.get("offset", 0)
-    base = (1 << 20) + 2 * off
-    assert xg.xgemm_kernel_family(M, N, K, base, lda, base, ldb, xg.xgemm_select_config(M, N, K, CODE[dtype], 256)) \
-        == xg.XGEMM_KERNEL_PIPELINED
+    cfg = xg.xgemm_select_config(M, N, K, CODE[dtype], 256)
+    copied = _copied(M, N, K, cfg, lda, ldb, off)
+    assert copied == {"n_odd": 2, "lda_not_x8": 1, "ldb_not_x8": 2}.get(name, 3)
     A, B, C_ref, S = _case(M, N, K, dtype, seed=M + N + K)
     nan = 0x7E00 if dtype == "fp16" else 0x7FC0
-    check_close(run_gpu(A, B, dtype, lda=lda, ldb=ldb, offset=off, pad=nan), C_ref, S,
-                "packed %s %s" % (name, dtype))
+    for what, c in (("packed", cfg), ("as called", None)):
+        check_close(run_gpu(A, B, dtype, config=c, lda=lda, ldb=ldb, offset=off, pad=nan), C_ref, S,
+                    "%s %s %s" % (what, name, dtype))
 
 
 @pytest.mark.parametrize("tile,split", [(0, 2), (1, 3), (2, 4)])
 def test_packed_operands_split_k(tile, split):
     M, N, K = 520, 601, 1533
+    assert _copied(M, N, K, config(tile, split), K + 3) == 3
     A, B, C_ref, S = _case(M, N, K, "bf16", seed=41 + split)
     check_close(run_gpu(A, B, "bf16", config=config(tile, split), lda=K + 3), C_ref, S,
                 "packed split tile %d split %d" % (tile, split))
@@ -180,6 +195,7 @@ def test_packed_operands_split_k(tile, split):
 
 def test_packed_operands_integer_bit_exact():
     M = N = K = 2047
+    assert _copied(M, N, K, None) == 3
     A, B = wl.make_int_inputs(M, N, K, "bf16", seed=42)
     C_ref, _ = oracle.gemm(A, B, "bf16")
     check_exact(run_gpu(A, B, "bf16"), C_ref, "integer, packed 2047^3")
@@ -188,10 +204,12 @@ def test_packed_operands_integer_bit_exact():
 def test_packed_then_aligned_calls_share_a_handle():
     """A packed call grows the workspace; aligned calls after it (and another
     packed call with a smaller shape) still see their own operands."""
-    cases = [(1000, 1001, 1024, 1), (512, 512, 512, 2), (700, 703, 705, 3)]
-    for M, N, K, seed in cases:
+    tile = config(xg.XGEMM_TILE_128x128)
+    cases = [(1000, 1001, 1024, tile, 1), (512, 512, 512, None, 2), (700, 703, 705, tile, 3)]
+    assert [_copied(M, N, K, cfg) for M, N, K, cfg, _ in cases] == [2, 0, 3]
+    for M, N, K, cfg, seed in cases:
         A, B, C_ref, S = _case(M, N, K, "fp16", seed=seed)
-        check_close(run_gpu(A, B, "fp16"), C_ref, S, "sequence %dx%dx%d" % (M, N, K))
+        check_close(run_gpu(A, B, "fp16", config=cfg), C_ref, S, "sequence %dx%dx%d" % (M, N, K))
 
 
 @pytest.mark.parametrize("split", [1, 2, 4, 8, 16])
@@ -221,7 +239,7 @@ def test_pipelined_integer_bit_exact(dtype):
 @pytest.mark.parametrize("split", [1, 2, 4, 8, 16])
 @pytest.mark.parametrize("tile", TILES)
 def test_split_k_factors(split, tile):
-    M, N, K = 384, 320, 4100  # K not a multiple of 32: the general kernel
+    M, N, K = 384, 320, 4100  # K not a multiple of 8: both operands copied
     A, B, C_ref, S = _case(M, N, K, "bf16", seed=split)
     check_close(run_gpu(A, B, "bf16", config=config(tile, split)), C_ref, S,
                 "tile %d split %d" % (tile, split))
@@ -316,7 +334,9 @@ def test_persistent_kernel_counters_left_zero():
     try:
         s = torch.cuda.current_stream().cuda_stream
         cases = [(1024, 1280, 1024, _sk_cfg(7), 61), (512, 520, 4096, config(xg.XGEMM_TILE_128x128, 4), 62),
-                 (1024, 1280, 1024, _sk_cfg(13), 63), (1000, 1001, 1024, None, 64), (2048, 2048, 768, _sk_cfg(60), 65)]
+                 (1024, 1280, 1024, _sk_cfg(13), 63), (1000, 1001, 1024, config(xg.XGEMM_TILE_128x128), 64),
+                 (2048, 2048, 768, _sk_cfg(60), 65)]
+        assert _copied(1000, 1001, 1024, cases[3][3]) == 2
         for rep in range(2):
             for M, N, K, cfg, seed in cases:
                 A, B, C_ref, S = _case(M, N, K, "bf16", seed=seed)
@@ -543,7 +563,8 @@ def _two_stream_cases():
     """Two calls that both use a workspace: a forced 4-way K split (partials
     in the workspace) and a packed B (N odd: B copied into the workspace)."""
     split = (512, 512, 4096, config(xg.XGEMM_TILE_128x128, 4), 71)
-    packed = (1000, 1001, 1024, None, 72)
+    packed = (1000, 1001, 1024, config(xg.XGEMM_TILE_128x128), 72)
+    assert _copied(*packed[:4]) == 2
     out = []
     for M, N, K, cfg, seed in (split, packed):
         A, B, C_ref, S = _case(M, N, K, "bf16", seed=seed)
@@ -809,6 +830,23 @@ def test_band_plan_equals_one_launch(shape):
 # strided batched products
 # ---------------------------------------------------------------------------
 
+# What each batch below runs on 256 CUs, as (L, M, N, K, pad of lda, shared B):
+# the batched plan has no query, so tests/test_plan_calls.py checks this table
+# on the host code.
+BATCH_ROUTES = {
+    (3, 512, 264, 1024, 0, False): "direct", (4, 300, 200, 100, 0, False): "direct",
+    (5, 64, 520, 320, 0, False): "direct", (6, 1024, 1032, 520, 0, False): "pipelined",
+    (3, 300, 201, 1000, 3, False): "direct", (3, 300, 201, 100, 3, False): "direct",
+    (5, 1100, 1001, 1000, 3, False): "copied", (3, 300, 7, 100, 3, False): "general",
+    (4, 256, 129, 512, 0, True): "direct", (7, 1001, 1003, 504, 0, True): "copied",
+}
+
+
+def _batches(lda_pad, shared_b):
+    """The (L, M, N, K) of the table with these layouts."""
+    return [s[:4] for s in BATCH_ROUTES if (s[4] > 0, s[5]) == (lda_pad, shared_b)]
+
+
 def _batched_case(L, M, N, K, dtype, seed, shared_a=False):
     As, Bs = [], []
     for b in range(L):
@@ -821,8 +859,7 @@ def _batched_case(L, M, N, K, dtype, seed, shared_a=False):
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "fp16"])
-@pytest.mark.parametrize("shape", [(3, 512, 264, 1024), (4, 300, 200, 100), (5, 64, 520, 320)],
-                         ids=lambda s: "x".join(map(str, s)))
+@pytest.mark.parametrize("shape", _batches(False, False), ids=lambda s: "x".join(map(str, s)))
 def test_strided_batched(dtype, shape):
     L, M, N, K = shape
     As, Bs = _batched_case(L, M, N, K, dtype, seed=L + M)
@@ -836,12 +873,13 @@ def test_strided_batched(dtype, shape):
         check_close(C[b], C_ref, S, "batch %d of %s" % (b, shape))
 
 
-@pytest.mark.parametrize("K", [1000, 100], ids=["copied", "general"])
-def test_strided_batched_unaligned(K):
-    """Odd N and a padded, odd lda: at K = 1000 every problem's operands are
-    copied into the workspace and the pipelined kernel runs; at K = 100 (two
-    K steps) the general kernel reads them in place."""
-    L, M, N = 3, 300, 201
+@pytest.mark.parametrize("shape", _batches(True, False), ids=lambda s: "x".join(map(str, s)))
+def test_strided_batched_unaligned(shape):
+    """Odd N and a padded, odd lda: small problems are read in place by the
+    register-direct kernel, or by the general one where N is below 8; larger
+    ones are copied into the workspace, every problem's, for the pipelined
+    kernel."""
+    L, M, N, K = shape
     As, Bs, refs = [], [], []
     for b in range(L):
         A, B, C_ref, S = _case(M, N, K, "bf16", seed=60 + b)
@@ -856,12 +894,14 @@ def test_strided_batched_unaligned(K):
     C = xg.bmm(Ad, Bd)
     torch.cuda.synchronize()
     for b in range(L):
-        check_close(C[b].cpu().numpy(), *refs[b], "batched unaligned K=%d problem %d" % (K, b))
+        check_close(C[b].cpu().numpy(), *refs[b], "batched unaligned %s problem %d" % (shape, b))
 
 
-def test_strided_batched_unaligned_shared_b():
-    """A shared B (stride 0) with odd N is copied once; A per problem."""
-    L, M, N, K = 4, 256, 129, 512
+@pytest.mark.parametrize("shape", _batches(False, True), ids=lambda s: "x".join(map(str, s)))
+def test_strided_batched_unaligned_shared_b(shape):
+    """A shared B (stride 0) with odd N: read in place, or copied once for all
+    problems."""
+    L, M, N, K = shape
     As, refs = [], []
     _, B, _, _ = _case(M, N, K, "fp16", seed=70)
     for b in range(L):

@@ -51,6 +51,14 @@ def test_batched_plans(host):
     host("batches")
 
 
+def test_batched_parity_cases_run_what_they_name(host):
+    """The kernels that the batched parity tests say they reach."""
+    from test_direct_kernel import BATCHES
+    from test_gpu_parity import BATCH_ROUTES
+    for case, route in {**BATCH_ROUTES, **{s + (0, False): "direct" for s in BATCHES}}.items():
+        assert host("batch_route", *(int(v) for v in case)).strip() == route, case
+
+
 def test_streaming_loads_of_b(host):
     """By B's size and only over rows that are whole cache lines."""
     host("streams")

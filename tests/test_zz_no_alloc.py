@@ -15,10 +15,13 @@ from paper_2609_16389_amd import xgemm as xg
 pytestmark = pytest.mark.gpu
 
 
-def _plan_scratch(M, N, K, dtype):
-    """Workspace bytes of xgemm_run's plan for these (aligned) arguments."""
-    band = xg.xgemm_select_band(M, N, K, CODE[dtype], 256)
-    return band, xg.xgemm_workspace_bytes(M, N, K, 256, band.body)
+def _launch(M, N, K):
+    """Workspace bytes of the launch xgemm_run makes for these (contiguous)
+    arguments, and which operands it copies (1: A, 2: B, 3: both)."""
+    assert xg.xgemm_select_band(M, N, K, xg.XGEMM_BF16, 256).axis == xg.XGEMM_BAND_NONE
+    cfg = xg.xgemm_launch_config(M, N, K, 1 << 20, K, 1 << 20, N, 256)
+    info = xg.xgemm_trace_plan(M, N, K, 1 << 20, K, 1 << 20, N, 1 << 20, N, cfg, 256, 0)
+    return xg.xgemm_workspace_bytes(M, N, K, 256, cfg), info.packed
 
 
 def _call(fn, h, M, N, K, dA, dB, C, dtype, s):
@@ -29,10 +32,12 @@ def _call(fn, h, M, N, K, dA, dB, C, dtype, s):
 @pytest.mark.parametrize("cases", [
     # split-k plans (partials in the scratch array), the second smaller
     [(1024, 1024, 16384, "bf16", 301), (512, 512, 8192, "bf16", 302)],
-    # operand copies (N or K odd: B, or both, copied into the scratch array)
+    # operand copies (N or K odd: both, or B, copied into the scratch array)
+    [(2047, 1999, 777, "fp16", 305), (1500, 1501, 1024, "fp16", 306)],
+    # the same layouts read in place, and one whose blocks the last workgroup of each tile adds
     [(1000, 1001, 1024, "fp16", 303), (300, 203, 777, "fp16", 304)],
-], ids=["split_k", "packed"])
-def test_noalloc_matches_xgemm_run(cases):
+], ids=["split_k", "packed", "in_place"])
+def test_noalloc_matches_xgemm_run(cases, request):
     oracle.build(force=False)
     h = xg.xgemm_create()
     try:
@@ -43,9 +48,11 @@ def test_noalloc_matches_xgemm_run(cases):
             C_ref, S = oracle.gemm(A, B, dtype)
             data.append((M, N, K, dtype, to_device(A, dtype), to_device(B, dtype), C_ref, S))
         # the scratch array is really used: split partials or copies
-        for M, N, K, dtype, *_ in data:
-            band, ws = _plan_scratch(M, N, K, dtype)
-            assert 0 < ws <= xg.XGEMM_NOALLOC_SCRATCH_BYTES or (N % 8 or K % 8), (M, N, K, band, ws)
+        used = [_launch(M, N, K) for M, N, K, *_ in data]
+        assert max(ws for ws, _ in used) <= xg.XGEMM_NOALLOC_SCRATCH_BYTES
+        assert [(ws > 0, packed) for ws, packed in used] == {
+            "split_k": [(True, 0), (True, 0)], "packed": [(True, 3), (True, 2)], "in_place": [(False, 0), (True, 0)],
+        }[request.node.callspec.id], used
         outs = [torch.full((M, N), float("nan"), dtype=torch.float32, device="cuda") for M, N, *_ in data]
         torch.cuda.synchronize()
         free0, _ = torch.cuda.mem_get_info()
