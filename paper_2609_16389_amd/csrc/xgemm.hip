@@ -507,8 +507,12 @@ double launch_cost(const LaunchCost &c, int64_t M, int64_t N, int64_t K, int64_t
                          (1.0 + (odd_a ? c.odd_a : 0.0) + (odd_b ? c.odd_b : 0.0));
     const int64_t rounds = n / slots, last = n % slots;
     double us = c.base + (double)rounds * (c.fixed + slabs * c.full);
+    // the share of the slots that run; but a K split that gives some CUs a second
+    // workgroup takes those CUs' time (27 x 17984 x 5696 with odd rows in 284
+    // workgroups of 32 x 256, 66.8 us, 56.5 with the tile plan: in 213, 45.3)
+    const double share = split > 1 && last > cu_count ? 1.0 : (double)last / (double)slots;
     if (last > 0)
-        us += c.fixed + slabs * (c.alone + (c.full - c.alone) * (double)last / (double)slots);
+        us += c.fixed + slabs * (c.alone + (c.full - c.alone) * share);
     // one CU draws 36 GB/s from beyond its L2 while it multiplies
     const double tbps = std::min(6.2e6, is_direct(c.tile) ? 0.036e6 * (double)std::min<int64_t>(n, cu_count) : 6.2e6);
     us = with_floor(us, 3.0 + operand_bytes(M, N, K, batch) / tbps + output_bytes(M, N, batch) / (c.c_tbps * 1e6));

@@ -207,6 +207,31 @@ int batches()
     return bad != 0 || replaced < 1000 || apply < 1000;
 }
 
+// Decoding steps of 17 to 64 rows: no K split that leaves some CUs with one
+// workgroup and gives a few (under three in eight) two.
+int doubled_up()
+{
+    std::mt19937 gen(17);
+    int bad = 0, splits = 0;
+    for (int i = 0; i < 4000; ++i) {
+        const int64_t N = 8192 + (int64_t)(gen() % 24576), K = 1024 + (int64_t)(gen() % 12288);
+        const Shape s{17 + (int64_t)(gen() % 48), N, K, K + (i % 2), N + (i % 3)};
+        CallPlan cp;
+        plan(s, true, 0, nullptr, &cp);
+        const Segment &g = cp.plan[0].seg[0];
+        if (!is_direct(cp.plan[0].tile) || g.p.split == 1)
+            continue;
+        ++splits;
+        if (cp.plan[0].tile == XGEMM_DIRECT_32x256 && g.grid > kCUs && g.grid < 11 * kCUs / 8) {
+            if (++bad < 10)
+                printf("%lld x %lld x %lld: %lld workgroups of 32 x 256, split %d\n", (long long)s.M, (long long)s.N,
+                       (long long)s.K, (long long)g.grid, g.p.split);
+        }
+    }
+    printf("%d of %d splits\n", bad, splits);
+    return bad != 0 || splits < 500;
+}
+
 // The launch a batch takes: L, M, N, K, the pad of A's rows, one B for all.
 int batch_route(char **v)
 {
@@ -261,6 +286,8 @@ int main(int argc, char **argv)
         return limits();
     if (!strcmp(what, "batches"))
         return batches();
+    if (!strcmp(what, "doubled_up"))
+        return doubled_up();
     if (!strcmp(what, "batch_route") && argc == 8)
         return batch_route(argv + 2);
     if (!strcmp(what, "streams"))

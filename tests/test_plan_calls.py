@@ -62,3 +62,8 @@ def test_batched_parity_cases_run_what_they_name(host):
 def test_streaming_loads_of_b(host):
     """By B's size and only over rows that are whole cache lines."""
     host("streams")
+
+
+def test_k_splits_of_decoding_steps(host):
+    """No K split that runs two workgroups on a few CUs and one on the others."""
+    host("doubled_up")
