@@ -232,6 +232,23 @@ int doubled_up()
     return bad != 0 || splits < 500;
 }
 
+// Odd rows of A under 64 x 64 blocks: the K splits that were slower than the
+// tile plan go to other launches, aligned rows keep theirs.
+int odd_rows()
+{
+    CallPlan odd, even;
+    int bad = 0;
+    for (const Shape &s : {Shape{493, 264, 18432, 18433, 264}, Shape{50, 5552, 2752, 2753, 5552},
+                           Shape{55, 6272, 2816, 2817, 6272}}) {
+        plan(s, true, 0, nullptr, &odd);
+        bad += odd.plan[0].tile == XGEMM_DIRECT_64x64 && odd.plan[0].seg[0].p.split > 1;
+    }
+    plan(Shape{384, 832, 6848, 6848, 832}, true, 0, nullptr, &even);
+    bad += even.plan[0].tile != XGEMM_DIRECT_64x64 || even.plan[0].seg[0].p.split != 3;
+    printf("%d wrong\n", bad);
+    return bad != 0;
+}
+
 // The launch a batch takes: L, M, N, K, the pad of A's rows, one B for all.
 int batch_route(char **v)
 {
@@ -288,6 +305,8 @@ int main(int argc, char **argv)
         return batches();
     if (!strcmp(what, "doubled_up"))
         return doubled_up();
+    if (!strcmp(what, "odd_rows"))
+        return odd_rows();
     if (!strcmp(what, "batch_route") && argc == 8)
         return batch_route(argv + 2);
     if (!strcmp(what, "streams"))

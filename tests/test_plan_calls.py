@@ -67,3 +67,8 @@ def test_streaming_loads_of_b(host):
 def test_k_splits_of_decoding_steps(host):
     """No K split that runs two workgroups on a few CUs and one on the others."""
     host("doubled_up")
+
+
+def test_k_splits_with_odd_rows(host):
+    """64 x 64 blocks are charged what odd rows of A cost them in a K split."""
+    host("odd_rows")
