@@ -446,10 +446,13 @@ BandPlan cached_band(PlanCache *cache, int64_t M, int64_t N, int64_t K, int cu_c
 // Fitted (least squares on log time) to 600 to 2700 timings of each over 790
 // shapes: M and N 1 .. 16384, K 64 .. 65536, batches up to 128, drawn evenly
 // over their logarithms, contiguous and padded, aligned and odd; rms error
-// 5-12%.  On those timed with the kernels as they are (some 510) the launches
-// it chooses are 1.72 times faster than the tile plans (geometric mean),
-// within 4% of the fastest candidate of each, and on 2 shapes 6-18% slower
-// than the tile plan.
+// 5-12% (bench.py --sweep times the same launches for given shapes).  Checked on
+// 2050 random products of other sizes, operands rotating over up to 0.9 GB:
+// where xgemm_run decides by it, it is 1.97 times faster than the tile plans
+// (geometric mean), within 4% of the fastest candidate of each, and on 13
+// shapes 3-18% slower than the tile plan.  The C rates are fitted over outputs
+// of all sizes: those that the last-level cache holds are modelled slow on both
+// sides (64 products of 256^3 12.5 us with the tile plan, measured 9.4).
 struct LaunchCost {
     int tile, slots_per_cu;
     int chains;     // partial sums per workgroup and element
@@ -475,7 +478,7 @@ constexpr LaunchCost kPlanCost[XGEMM_TILE_COUNT] = {
 };
 constexpr int kLaunchSplits[] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32};
 // a launch replaces the tile plan only if it is modelled this much faster
-// (at 1.0, 5 of the shapes were 6-17% slower than the tile plan)
+// (at 1.0, 5 of the 790 shapes were 6-17% slower than the tile plan)
 constexpr double kLaunchMargin = 0.94;
 
 // A time that is neither below `us` nor below the bytes' time.
@@ -528,9 +531,9 @@ double launch_cost(const LaunchCost &c, int64_t M, int64_t N, int64_t K, int64_t
 
 // Modelled time of the tile plan `cfg` for these operands: the geometric mean
 // of the two models (the tile model alone is 10-20% low on one round of 128 x
-// 128 tiles, the launch model 10-40% high on short K; between them 2 of the
-// 580 shapes lose by more than 3%).  No call is faster than its bytes at 4.3 TB/s (few rows leave most of each
-// tile's loads to A's last row), plus the copies of operands the pipelined
+// 128 tiles, the launch model 10-40% high on short K).  No call is faster than
+// its bytes at 4.3 TB/s (few rows leave most of each tile's loads to A's last
+// row), plus the copies of operands the pipelined
 // kernels cannot read in place; for K ranges under three steps, the general
 // kernel's rounds.  Fitted to the same shapes as the launches.
 double plan_cost(int64_t M, int64_t N, int64_t K, bool copy_a, bool copy_b, int64_t batch, const xgemm_config &cfg,
