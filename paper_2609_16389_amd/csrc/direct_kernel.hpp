@@ -32,7 +32,9 @@
 // 8 waves hold 9 KiB each).  With few tiles, latency: 256^3 3.7 us against
 // 6.0, 1000^3 9.5 against 20.9 (256 workgroups against 64).  With many tiles
 // the L1 path, through which every wave pulls its own operands (64 x 128: 43
-// flop per byte), where the LDS tiles win: 2048^3 33 us against 27.  Odd
+// flop per byte), where the LDS tiles win: 2048^3 33 us against 27 (12.8M L1
+// accesses against the wave-pair tile's 5.2M; the L1's data return is the
+// busiest unit, 60% of the time, the matrix cores 17%).  Odd
 // rows cost a slab 1.2-1.5 times its time (each 16-byte load then straddles
 // dwords); a copy of the operands costs more: 16 x 10376 x 8656 with odd
 // rows 42 us against 157.  A K split over the waves of a workgroup first,

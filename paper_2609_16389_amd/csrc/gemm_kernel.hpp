@@ -1123,9 +1123,9 @@ __host__ __device__ __forceinline__ void dma_tile(const Ops &ops, const GemmPara
         // read during step t into the other register buffer, so the buffer
         // alternates with the step's parity (a template argument: register
         // arrays are not indexed at run time).  128 x 128 with four stages:
-        // 0.35 us a K step with one CU at work (the LDS port: 32 KiB in, 64 KiB
-        // out), 0.43 with all (2048 x 2048 x 8192, 1.07 PFLOP/s; 0.41 on zeros),
-        // against 0.6-0.7 for four waves and two stages; 2048^3 22.4 against
+        // 0.35 us a K step with one CU at work (32 KiB into LDS, 64 KiB out), 0.43
+        // with all (2048 x 2048 x 8192, 1.07 PFLOP/s; 0.41 on zeros; at 2048^3 no
+        // unit is busy half the time, the matrix cores 26%), against 0.6-0.7 for four waves and two stages; 2048^3 22.4 against
         // 27.0 us, of which 8 are the launch, the first loads and C.
         constexpr int R = 1;                      // rows of a step issued before its barrier
         static_assert(MI == 16 && STAGES >= 3 && STAGES <= 4 && KS == 2 && FM % 2 == 0, "K-pair schedule shape");
