@@ -1125,8 +1125,9 @@ __host__ __device__ __forceinline__ void dma_tile(const Ops &ops, const GemmPara
         // arrays are not indexed at run time).  128 x 128 with four stages:
         // 0.35 us a K step with one CU at work (32 KiB into LDS, 64 KiB out), 0.43
         // with all (2048 x 2048 x 8192, 1.07 PFLOP/s; 0.41 on zeros; at 2048^3 no
-        // unit is busy half the time, the matrix cores 26%), against 0.6-0.7 for four waves and two stages; 2048^3 22.4 against
-        // 27.0 us, of which 8 are the launch, the first loads and C.
+        // unit is busy half the time, the matrix cores 26%), against 0.6-0.7 for
+        // four waves and two stages; 2048^3 22.4 against 27.0 us, of which 8 are
+        // the launch, the first loads and C.
         constexpr int R = 1;                      // rows of a step issued before its barrier
         static_assert(MI == 16 && STAGES >= 3 && STAGES <= 4 && KS == 2 && FM % 2 == 0, "K-pair schedule shape");
         constexpr int BR = (FN + FM - R - 1) / (FM - R);   // B blocks read per row after the barrier
