@@ -515,8 +515,11 @@ double launch_cost(const LaunchCost &c, int64_t M, int64_t N, int64_t K, int64_t
     double us = c.base + (double)rounds * (c.fixed + slabs * c.full);
     // the share of the slots that run; but a K split that gives some CUs a second
     // workgroup takes those CUs' time (27 x 17984 x 5696 with odd rows in 284
-    // workgroups of 32 x 256, 66.8 us, 56.5 with the tile plan: in 213, 45.3)
-    const double share = split > 1 && last > cu_count ? 1.0 : (double)last / (double)slots;
+    // workgroups of 32 x 256, 66.8 us, 56.5 with the tile plan: in 213, 45.3).
+    // Not of a tile plan: at 960 x 257 x 60048 its 384 workgroups take 84 us, the
+    // wave-pair tile that the higher price would choose 100.
+    const bool doubled = is_direct(c.tile) && split > 1 && last > cu_count;
+    const double share = doubled ? 1.0 : (double)last / (double)slots;
     if (last > 0)
         us += c.fixed + slabs * (c.alone + (c.full - c.alone) * share);
     // one CU draws 36 GB/s from beyond its L2 while it multiplies

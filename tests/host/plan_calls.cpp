@@ -228,6 +228,13 @@ int doubled_up()
                        (long long)s.K, (long long)g.grid, g.p.split);
         }
     }
+    // the price of a tile plan whose split does so is its own measurement: K
+    // splits of 128 x 128 tiles keep their place against other launches
+    for (const Shape &s : {Shape{960, 257, 60048, 60048, 257}, Shape{2112, 763, 5160, 5160, 763}}) {
+        CallPlan cp;
+        plan(s, true, 0, nullptr, &cp);
+        bad += cp.plan[0].tile != XGEMM_TILE_128x128;
+    }
     printf("%d of %d splits\n", bad, splits);
     return bad != 0 || splits < 500;
 }
